@@ -461,8 +461,9 @@ __global__ __launch_bounds__(256) void merge_finish_banded(int32_t T, const int3
 // (fixed butterfly), and the chunk's last run, when it goes on past the
 // chunk, by reading on 64 entries at a time, adding each chunk in order.  A
 // run that began in an earlier chunk belongs to that chunk's wavefront.  The
-// run total is added to its row of y (kc columns).  Deterministic: no
-// atomics, one writer per row.
+// run total is added to its row of y, column blockIdx.y of kc: with the
+// columns one after the other in a wavefront, eight took 12 us on 10k units.
+// Deterministic: no atomics, one writer per element.
 __global__ __launch_bounds__(256) void merge_fixup(int32_t T, int32_t rows, int32_t kc,
                                                    const int32_t *__restrict__ carry_row,
                                                    const float *__restrict__ carry_val,
@@ -478,7 +479,8 @@ __global__ __launch_bounds__(256) void merge_fixup(int32_t T, int32_t rows, int3
     // the last lane's run goes on into the next chunk
     const bool open = __ballot(lane == kWave - 1 && in && !tail) != 0;
     const int32_t r_open = __shfl(r, kWave - 1);
-    for (int32_t c = 0; c < kc; ++c) {
+    {
+        const int32_t c = blockIdx.y;
         const seg_t sc = group_seg_scan_incl<kWave>(seg_t{in ? carry_val[b * kc + c] : 0.f, head});
         // sc.f: some run starts at or before this lane inside the chunk, so
         // a tail lane with sc.f ends a run that this chunk owns
@@ -505,7 +507,7 @@ hipError_t launch_fixup(int64_t T, int32_t rows, int32_t kc, const int32_t *carr
     if (T <= 0) return hipSuccess;
     prof_scope p(s, tag);
     const int64_t blocks = (T + 255) / 256;  // one wavefront per 64 entries
-    hipLaunchKernelGGL(merge_fixup, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s,
+    hipLaunchKernelGGL(merge_fixup, dim3(static_cast<uint32_t>(blocks), kc), dim3(256), 0, s,
                        static_cast<int32_t>(T), rows, kc, carry_row, carry_val, y, ldy);
     return hipGetLastError();
 }

@@ -300,7 +300,10 @@ lb_schedule_t heuristic(const lb_csr_t *A) {
     return s;
 }
 
-lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_schedule_t *out) {
+// *default_units: a merge-path schedule whose units the caller (or its tuned
+// pick) left open.
+lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_schedule_t *out,
+                    bool *default_units = nullptr) {
     if (!in || !out) return LB_ERR_INVALID_ARG;
     lb_schedule_t s = *in;
     if (s.kind == LB_AUTO) {
@@ -314,6 +317,7 @@ lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_sc
     }
     const lb_status_t st = fill_defaults(&s, out);
     if (st != LB_OK) return st;
+    if (default_units) *default_units = out->kind == LB_MERGE_PATH && s.block_size == 0 && s.items_per_thread == 0;
     // column bands and vector loads: lb_spmv only
     if ((out->x_bands != 1 || out->vector_width != 1) && k != 1) return LB_ERR_UNSUPPORTED;
     if (out->kind == LB_MERGE_PATH && k == 1 && s.block_size == 0 && s.items_per_thread == 0 && out->x_bands == 1 &&
@@ -333,13 +337,27 @@ lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_sc
     return LB_OK;
 }
 
+// Units of a product with k > 1 columns whose units were left open: half the
+// default.  A group of lanes walks its items one after the other (64 items in
+// each of 8 groups of a wavefront at k = 32 and 256 x 8), so shorter units end
+// sooner and small matrices fill more CUs.  256 x 4 against 256 x 8, us a call:
+// 5000 power-law rows, k = 64 20.9 / 30.8; 20,000 uniform rows, k = 13
+// 14.0 / 16.7; 490,000-row stencil, k = 8 28.4 / 34.3; 500,003 power-law rows,
+// k = 32 240.0 / 240.9.
+void spmm_units(int32_t k, bool default_units, lb_schedule_t *r) {
+    if (k > 1 && default_units) r->items_per_thread = kDefaultItems / 2;
+}
+
 // Entry points other than lb_spmv take the plain merge-path consume only
 // (one column band, one nonzero per lane and load).
 lb_status_t one_band(const lb_schedule_t &s) {
     return s.x_bands == 1 && s.vector_width == 1 ? LB_OK : LB_ERR_UNSUPPORTED;
 }
 
-int spmm_pass_cols(int32_t k) { return k >= 8 ? 8 : (k >= 4 ? 4 : (k >= 2 ? 2 : 1)); }
+// Columns of X whose carries the narrowest workspace of a k-column product
+// holds.  A workspace of the full size (k columns of carries) runs the product
+// in one pass over the matrix; one that holds only these runs ceil(k / 8).
+int32_t spmm_narrow_cols(int32_t k) { return k >= 8 ? 8 : (k >= 4 ? 4 : (k >= 2 ? 2 : 1)); }
 
 size_t ws_bytes_for(const lb_csr_t *A, const lb_schedule_t &s, int32_t k) {
     if (s.kind == LB_WORK_QUEUE) return 256;  // the queue's counter
@@ -347,7 +365,7 @@ size_t ws_bytes_for(const lb_csr_t *A, const lb_schedule_t &s, int32_t k) {
     const int64_t W = static_cast<int64_t>(s.block_size) * s.items_per_thread;
     const int64_t T = lbk::merge_units(A->rows, A->nnz, W);
     if (s.x_bands == 2) return lbk::merge_banded_ws_bytes(T, A->rows);
-    return lbk::merge_ws_bytes(T, k <= 0 ? 1 : spmm_pass_cols(k));
+    return lbk::merge_ws_bytes(T, k <= 0 ? 1 : k);
 }
 
 // ------------------------------------------------------------------ COO and CSC
@@ -833,8 +851,10 @@ LB_API lb_status_t lb_workspace_size(const lb_csr_t *A, const lb_schedule_t *s, 
     lb_status_t st = check_csr(A);
     if (st != LB_OK) return st;
     lb_schedule_t r;
-    st = resolve(A, k, s, &r);
+    bool default_units = false;
+    st = resolve(A, k, s, &r, &default_units);
     if (st != LB_OK) return st;
+    spmm_units(k, default_units, &r);
     if (k == 0) {  // backward always runs on the merge-path split
         if (r.kind != LB_MERGE_PATH) {
             lb_schedule_t m{};
@@ -1341,10 +1361,16 @@ LB_API lb_status_t lb_spmm(const lb_csr_t *A, const void *X, lb_dtype_t x_dtype,
     if (x_dtype != A->value_dtype) return LB_ERR_UNSUPPORTED;
     if (A->cols * ldx > (int64_t(1) << 40) || A->rows * ldy > (int64_t(1) << 40)) return LB_ERR_OVERFLOW;
     lb_schedule_t r;
-    st = resolve(A, k, s, &r);
+    bool default_units = false;
+    st = resolve(A, k, s, &r, &default_units);
     if (st != LB_OK) return st;
+    spmm_units(k, default_units, &r);
     if (r.kind == LB_GROUP_MAPPED || r.kind == LB_WORK_QUEUE || one_band(r) != LB_OK) return LB_ERR_UNSUPPORTED;
-    const size_t need = ws_bytes_for(A, r, k);
+    // a smaller workspace runs the product in passes, then in longer units
+    int32_t kc = k;
+    if (workspace_bytes < ws_bytes_for(A, r, kc)) kc = spmm_narrow_cols(k);
+    if (k > 1 && default_units && workspace_bytes < ws_bytes_for(A, r, kc)) r.items_per_thread = kDefaultItems;
+    const size_t need = ws_bytes_for(A, r, kc);
     if (need > 0 && (workspace_bytes < need || !workspace)) return LB_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     if (A->rows == 0) return LB_OK;
@@ -1356,7 +1382,7 @@ LB_API lb_status_t lb_spmm(const lb_csr_t *A, const void *X, lb_dtype_t x_dtype,
     }
     if (r.kind == LB_THREAD_MAPPED)
         return hip_status(lbk::thread_mapped_spmm(d, X, k, ldx, Y, ldy, r.block_size, r.grid_size, hs));
-    return hip_status(lbk::merge_spmm(d, X, k, ldx, Y, ldy, r.block_size, r.items_per_thread, workspace, hs));
+    return hip_status(lbk::merge_spmm(d, X, k, ldx, Y, ldy, r.block_size, r.items_per_thread, workspace, kc, hs));
 }
 
 LB_API lb_status_t lb_spmv_backward(const lb_csr_t *A, const void *x, lb_dtype_t x_dtype, const float *dy, float *dx,
@@ -1418,7 +1444,8 @@ static lbk::batch_dev to_dev(const lb_batch_t *B) {
     return d;
 }
 
-static lb_status_t resolve_batched(const lb_batch_t *B, int32_t k, const lb_schedule_t *s, lb_schedule_t *out) {
+static lb_status_t resolve_batched(const lb_batch_t *B, int32_t k, const lb_schedule_t *s, lb_schedule_t *out,
+                                   bool *default_units) {
     lb_schedule_t in = s ? *s : lb_schedule_t{LB_AUTO, 0, 0, 0, 0, 0};
     if (in.kind == LB_AUTO) {
         lb_schedule_t tuned;
@@ -1431,17 +1458,34 @@ static lb_status_t resolve_batched(const lb_batch_t *B, int32_t k, const lb_sche
     }
     if (in.kind != LB_MERGE_PATH) return LB_ERR_UNSUPPORTED;
     const lb_status_t st = fill_defaults(&in, out);
-    return st != LB_OK ? st : one_band(*out);
+    if (st != LB_OK) return st;
+    *default_units = in.block_size == 0 && in.items_per_thread == 0;
+    if (k > 1 && *default_units) {
+        // More columns: with 512 x 8 a CU has 16 wavefronts (of 20 with 256 x 8)
+        // on half as many places of the batch, and the X rows of those stay in
+        // L2 (159M misses against 246M).  512 matrices, 436M nonzeros, k = 8:
+        // 3.37 ms, 256 x 8 4.36; 207M nonzeros, k = 11 1.95 / 2.55, k = 2
+        // 0.92 / 1.06.  Fewer than four such units a CU leave it idle: 32
+        // matrices, 0.55M nonzeros, 17.4 us against 14.9 with 256 x 4.
+        const bool large = lbk::merge_units(B->total_rows, B->total_nnz, 512 * 8) >= 1024;
+        out->block_size = large ? 512 : 256;
+        out->items_per_thread = large ? 8 : 4;
+    }
+    return one_band(*out);
 }
+
+// A batched workspace holds at least this many columns' carries, whatever k.
+static constexpr int32_t kBatchedNarrow = 8;
 
 LB_API lb_status_t lb_batched_workspace_size(const lb_batch_t *B, const lb_schedule_t *s, int32_t k, size_t *bytes) {
     if (!bytes || k < 1 || k > kMaxK) return LB_ERR_INVALID_ARG;
     lb_status_t st = check_batch(B);
     if (st != LB_OK) return st;
     lb_schedule_t r;
-    st = resolve_batched(B, k, s, &r);
+    bool default_units = false;
+    st = resolve_batched(B, k, s, &r, &default_units);
     if (st != LB_OK) return st;
-    *bytes = lbk::batched_ws_bytes(to_dev(B), r.block_size, r.items_per_thread, k);
+    *bytes = lbk::batched_ws_bytes(to_dev(B), r.block_size, r.items_per_thread, std::max(k, kBatchedNarrow));
     return LB_OK;
 }
 
@@ -1454,15 +1498,23 @@ LB_API lb_status_t lb_batched_spmm(const lb_batch_t *B, const void *X, lb_dtype_
     if (B->total_nnz > 0 && !X) return LB_ERR_INVALID_ARG;
     if (x_dtype != B->value_dtype) return LB_ERR_UNSUPPORTED;
     lb_schedule_t r;
-    st = resolve_batched(B, k, s, &r);
+    bool default_units = false;
+    st = resolve_batched(B, k, s, &r, &default_units);
     if (st != LB_OK) return st;
     const lbk::batch_dev d = to_dev(B);
-    const size_t need = lbk::batched_ws_bytes(d, r.block_size, r.items_per_thread, k);
+    int32_t kc = std::max(k, kBatchedNarrow);
+    if (workspace_bytes < lbk::batched_ws_bytes(d, r.block_size, r.items_per_thread, kc)) kc = kBatchedNarrow;
+    // (units chosen by the caller or its tuned pick fit their own size)
+    if (k > 1 && default_units && workspace_bytes < lbk::batched_ws_bytes(d, r.block_size, r.items_per_thread, kc)) {
+        r.block_size = kDefaultBlock;
+        r.items_per_thread = kDefaultItems;
+    }
+    const size_t need = lbk::batched_ws_bytes(d, r.block_size, r.items_per_thread, kc);
     if (need > 0 && (workspace_bytes < need || !workspace)) return LB_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     if (B->total_rows == 0) return LB_OK;
     if (B->total_nnz == 0) return hip_status(lbk::fill_f32(Y, B->total_rows * k, 0.f, hs));
-    return hip_status(lbk::batched_spmm(d, X, k, Y, r.block_size, r.items_per_thread, workspace, hs));
+    return hip_status(lbk::batched_spmm(d, X, k, Y, r.block_size, r.items_per_thread, workspace, kc, hs));
 }
 
 // ------------------------------------------------------------------ test hooks
@@ -1508,16 +1560,20 @@ LB_API lb_status_t lb_validate_csr(const lb_csr_t *A, void *stream) {
 
 // ------------------------------------------------------------------ autotune
 
+// The largest candidate workspace with kc columns of carries: the smallest
+// merge-path unit, or the two-band candidates' (units of at least 2048 items,
+// plus a rows buffer).
+static size_t autotune_ws_bytes(const lb_csr_t *A, int32_t k, int32_t kc) {
+    const size_t one = lbk::merge_ws_bytes(lbk::merge_units(A->rows, A->nnz, 128 * 4), kc);
+    const size_t two = k == 1 ? lbk::merge_banded_ws_bytes(lbk::merge_units(A->rows, A->nnz, 2048), A->rows) : 0;
+    return one > two ? one : two;
+}
+
 LB_API lb_status_t lb_autotune_workspace_size(const lb_csr_t *A, int32_t k, size_t *bytes) {
     if (!bytes || k < 1 || k > kMaxK) return LB_ERR_INVALID_ARG;
     lb_status_t st = check_csr(A);
     if (st != LB_OK) return st;
-    // the largest candidate workspace: the smallest merge-path unit, or the
-    // two-band candidates' (units of at least 2048 items, plus a rows buffer)
-    const int64_t T = lbk::merge_units(A->rows, A->nnz, 128 * 4);
-    const size_t one = lbk::merge_ws_bytes(T, spmm_pass_cols(k));
-    const size_t two = k == 1 ? lbk::merge_banded_ws_bytes(lbk::merge_units(A->rows, A->nnz, 2048), A->rows) : 0;
-    *bytes = one > two ? one : two;
+    *bytes = autotune_ws_bytes(A, k, k);
     return LB_OK;
 }
 
@@ -1527,9 +1583,8 @@ LB_API lb_status_t lb_autotune(const lb_csr_t *A, const void *X, lb_dtype_t x_dt
     lb_status_t st = check_csr(A);
     if (st != LB_OK) return st;
     if (!best || k < 1 || k > kMaxK) return LB_ERR_INVALID_ARG;
-    size_t need = 0;
-    lb_autotune_workspace_size(A, k, &need);
-    if (workspace_bytes < need || !workspace) return LB_ERR_WORKSPACE_TOO_SMALL;
+    // a workspace of narrow carries times the passes that lb_spmm runs with it
+    if (workspace_bytes < autotune_ws_bytes(A, k, spmm_narrow_cols(k)) || !workspace) return LB_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     uint64_t fp = 0;
     st = fingerprint(A->rows, A->cols, A->nnz, A->row_offsets, A->col_idx, nullptr, 0, hs, &fp);

@@ -253,67 +253,6 @@ __device__ __forceinline__ seg_t block_seg_scan_excl(seg_t x, seg_t *s_wave, seg
     return lane ? seg_combine(pre, seg_t{pv, pf}) : pre;
 }
 
-// Block-wide exclusive segmented scan of KC values sharing one flag per
-// thread (the same operator as seg_t), in one pass: KC values per shuffle
-// step and one LDS exchange, so two barriers whatever KC is.  s_wv holds
-// BLOCK/64 * KC floats, s_wf BLOCK/64 ints.  ex[c] = exclusive prefix,
-// tot[c] = block total; ends with a barrier.
-template <int BLOCK, int KC>
-__device__ __forceinline__ void block_seg_scan_excl_kc(const float (&v)[KC], int flag, float (&ex)[KC],
-                                                       float (&tot)[KC], float *s_wv, int *s_wf) {
-    constexpr int NW = BLOCK / kWave;
-    const int lane = lane_id(), w = wave_id();
-    float inc[KC];
-#pragma unroll
-    for (int c = 0; c < KC; ++c) inc[c] = v[c];
-    int f = flag;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int pf = __shfl_up(f, off, kWave);
-        float pv[KC];
-#pragma unroll
-        for (int c = 0; c < KC; ++c) pv[c] = __shfl_up(inc[c], off, kWave);
-        if (lane >= off) {
-#pragma unroll
-            for (int c = 0; c < KC; ++c) inc[c] = f ? inc[c] : pv[c] + inc[c];
-            f |= pf;
-        }
-    }
-    if (lane == kWave - 1) {
-        s_wf[w] = f;
-#pragma unroll
-        for (int c = 0; c < KC; ++c) s_wv[w * KC + c] = inc[c];
-    }
-    __syncthreads();
-    float pre[KC], all[KC];
-    int pre_f = 0, all_f = 0;
-#pragma unroll
-    for (int c = 0; c < KC; ++c) pre[c] = all[c] = 0.f;
-#pragma unroll
-    for (int k = 0; k < NW; ++k) {
-        const int fk = s_wf[k];
-#pragma unroll
-        for (int c = 0; c < KC; ++c) {
-            const float vk = s_wv[k * KC + c];
-            if (k < w) pre[c] = fk ? vk : pre[c] + vk;
-            all[c] = fk ? vk : all[c] + vk;
-        }
-        if (k < w) pre_f |= fk;
-        all_f |= fk;
-    }
-    __syncthreads();
-    // exclusive within the wavefront: the inclusive value of the lane before
-    const int ef = __shfl_up(f, 1, kWave);
-#pragma unroll
-    for (int c = 0; c < KC; ++c) {
-        const float ev = __shfl_up(inc[c], 1, kWave);
-        ex[c] = lane ? (ef ? ev : pre[c] + ev) : pre[c];
-        tot[c] = all[c];
-    }
-    (void)pre_f;
-    (void)all_f;
-}
-
 // Block-wide sum (all threads call; every thread gets the total).  s_red
 // holds BLOCK/64 floats.  Waves are added in index order: deterministic.
 template <int BLOCK>

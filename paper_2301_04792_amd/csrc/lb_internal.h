@@ -219,8 +219,9 @@ hipError_t merge_spmv_planned_consume(const csr_dev &A, const plan_dev &pl, cons
 // y = A x with a built plan; ws holds plan_ws_bytes(...).
 hipError_t planned_spmv(const csr_dev &A, const plan_dev &pl, const void *x, float *y, void *ws, hipStream_t s);
 
+// The workspace is merge_ws_bytes(T, kc_max): passes of at most kc_max columns.
 hipError_t merge_spmm(const csr_dev &A, const void *X, int32_t k, int64_t ldx, float *Y, int64_t ldy,
-                      int block, int items, void *ws, hipStream_t s);
+                      int block, int items, void *ws, int32_t kc_max, hipStream_t s);
 
 // combine_dx (dx only): products are summed per target in LDS before the
 // global atomics (for scatters whose targets repeat within a unit).
@@ -238,9 +239,10 @@ struct batch_dev {
     const int64_t *nnz_base;
     const int64_t *col_base;
 };
-size_t batched_ws_bytes(const batch_dev &B, int block, int items, int k);
+// Workspace for passes of at most kc columns.
+size_t batched_ws_bytes(const batch_dev &B, int block, int items, int kc);
 hipError_t batched_spmm(const batch_dev &B, const void *X, int32_t k, float *Y, int block, int items,
-                        void *ws, hipStream_t s);
+                        void *ws, int32_t kc_max, hipStream_t s);
 
 // ---- thread- and group-mapped ---------------------------------------------------------
 hipError_t thread_mapped_spmv(const csr_dev &A, const void *x, float *y, int block, int grid,
