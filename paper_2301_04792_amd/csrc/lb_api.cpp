@@ -368,6 +368,12 @@ size_t ws_bytes_for(const lb_csr_t *A, const lb_schedule_t &s, int32_t k) {
     return lbk::merge_ws_bytes(T, k <= 0 ? 1 : k);
 }
 
+// Workspace of the scatter by bins for A's dx (0 where it does not pay).  A
+// call with less workspace scatters with float atomics.
+size_t scatter_ws_bytes(const lb_csr_t *A) {
+    return lbk::bins_pay(A->cols, A->nnz) ? lbk::bins_ws_bytes(A->rows, A->cols, A->nnz) : 0;
+}
+
 // ------------------------------------------------------------------ COO and CSC
 
 lb_status_t check_coo(const lb_coo_t *A) {
@@ -863,6 +869,7 @@ LB_API lb_status_t lb_workspace_size(const lb_csr_t *A, const lb_schedule_t *s, 
         }
     }
     *bytes = ws_bytes_for(A, r, k);
+    if (k == 0) *bytes = std::max(*bytes, scatter_ws_bytes(A));
     return LB_OK;
 }
 
@@ -1302,7 +1309,7 @@ LB_API lb_status_t lb_csc_workspace_size(const lb_csc_t *A, const lb_schedule_t 
     lb_schedule_t r;
     st = csc_schedule(s, &r);
     if (st != LB_OK) return st;
-    *bytes = ws_bytes_for(&c, r, 0);
+    *bytes = std::max(ws_bytes_for(&c, r, 0), scatter_ws_bytes(&c));
     return LB_OK;
 }
 
@@ -1321,6 +1328,10 @@ LB_API lb_status_t lb_spmv_csc(const lb_csc_t *A, const void *x, lb_dtype_t x_dt
     if (workspace_bytes < need || !workspace) return LB_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     if (A->rows == 0) return LB_OK;
+    const size_t bins = scatter_ws_bytes(&c);
+    if (bins > 0 && workspace_bytes >= bins)
+        return hip_status(lbk::binned_backward(to_dev(&c), nullptr, static_cast<const float *>(x), y, nullptr,
+                                               workspace, hs));
     hipError_t e = lbk::fill_f32(y, A->rows, 0.f, hs);
     if (e != hipSuccess || A->nnz == 0) return hip_status(e);
     // the scatter of the backward pass: columns are its tiles, x its per-tile
@@ -1403,6 +1414,9 @@ LB_API lb_status_t lb_spmv_backward(const lb_csr_t *A, const void *x, lb_dtype_t
     const size_t need = ws_bytes_for(A, r, 0);
     if (workspace_bytes < need || !workspace) return LB_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
+    const size_t bins = dx ? scatter_ws_bytes(A) : 0;
+    if (bins > 0 && workspace_bytes >= bins)
+        return hip_status(lbk::binned_backward(to_dev(A), x, dy, dx, dvalues, workspace, hs));
     if (dx) {
         hipError_t e = lbk::fill_f32(dx, A->cols, 0.f, hs);
         if (e != hipSuccess) return hip_status(e);

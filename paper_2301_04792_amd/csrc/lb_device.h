@@ -42,6 +42,15 @@ __device__ __forceinline__ T ld_stream(const T *p) {
     return __builtin_nontemporal_load(p);
 }
 
+// Element i of an array whose start is the same for all lanes: a 32-bit byte
+// offset from a scalar base, one address register instead of a 64-bit pair.
+// i * sizeof(T) must fit 32 bits.
+template <typename T>
+__device__ __forceinline__ T *at_off(T *base, uint32_t i) {
+    using bytes = std::conditional_t<std::is_const_v<T>, const char, char>;
+    return reinterpret_cast<T *>(reinterpret_cast<bytes *>(base) + i * static_cast<uint32_t>(sizeof(T)));
+}
+
 // Four consecutive elements as one vector load (16 bytes of float, 8 of BF16).
 template <typename T>
 struct vec4_of;

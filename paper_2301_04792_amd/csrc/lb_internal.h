@@ -83,10 +83,11 @@ inline merge_ws merge_ws_carve(void *base, int64_t T) {
 
 // The split at every unit boundary.  With row_base (a batch's int64 row
 // prefix sums, count + 1 entries) it also writes part_mat[t], the matrix
-// owning row min(part_i[t], rows - 1).
+// owning row min(part_i[t], rows - 1).  clear: nclear floats set to 0.
 hipError_t merge_partition(const int32_t *ro, int32_t rows, int32_t nnz, int32_t W, int32_t T,
                            int32_t *part_i, int32_t *part_j, hipStream_t s, const int64_t *row_base = nullptr,
-                           int32_t count = 0, int32_t *part_mat = nullptr);
+                           int32_t count = 0, int32_t *part_mat = nullptr, float *clear = nullptr,
+                           int32_t nclear = 0);
 
 // True if (block, items) is an instantiated merge-path configuration.
 bool merge_config_supported(int block, int items);
@@ -227,6 +228,21 @@ hipError_t merge_spmm(const csr_dev &A, const void *X, int32_t k, int64_t ldx, f
 // global atomics (for scatters whose targets repeat within a unit).
 hipError_t merge_backward(const csr_dev &A, const void *x, const float *dy, float *dx, float *dvalues,
                           int block, int items, void *ws, hipStream_t s, bool combine_dx = false);
+
+// ---- the backward's scatter by bins (k_bins.hip) ----------------------------------------
+// Whether dx (A.cols targets, written whole) is summed by bins.  us, by bins and
+// by float atomics (backward with dvalues): 0.23M power-law nonzeros 24.4 / 20.8,
+// 0.48M uniform 22.3 / 39.3, 6.6M power-law 99 / 275, 32M uniform 348 / 1552, 32M
+// over 1000 columns 181 / 7934; a stencil of 5.2M 61.2 / 59.2.  CSC product:
+// 0.45M stencil 17.1 / 23.3, 30.8M power-law 214 / 959.  At most 512 bins (4.2M
+// targets): runs of a unit's bin are short past that (20M nonzeros over 4M
+// columns 543 / 988).
+constexpr int64_t kBinMinNnz = 400000;
+bool bins_pay(int64_t n, int64_t nnz);
+size_t bins_ws_bytes(int64_t rows, int64_t n, int64_t nnz);
+// As merge_backward with dx; dx need not be cleared.  Needs bins_pay.
+hipError_t binned_backward(const csr_dev &A, const void *x, const float *dy, float *dx, float *dvalues, void *ws,
+                           hipStream_t s);
 
 // ---- batched ------------------------------------------------------------------------
 struct batch_dev {
