@@ -24,11 +24,12 @@
 namespace lbk {
 using namespace lb;
 
-template <int BLOCK, int ITEMS, typename VT, bool WANT_DX, bool WANT_DV, bool COMBINE = false>
+// WANT_PROD: also the products values[j] * dy[row(j)], in order.
+template <int BLOCK, int ITEMS, typename VT, bool WANT_DX, bool WANT_DV, bool COMBINE = false, bool WANT_PROD = false>
 __global__ __launch_bounds__(BLOCK) void merge_backward_kernel(
     int32_t rows, int32_t nnz, const int32_t *__restrict__ ro, const int32_t *__restrict__ ci, const VT *__restrict__ val,
     const VT *__restrict__ x, const float *__restrict__ dy, float *__restrict__ dx, float *__restrict__ dvalues,
-    const int32_t *__restrict__ part_i, const int32_t *__restrict__ part_j) {
+    const int32_t *__restrict__ part_i, const int32_t *__restrict__ part_j, float *__restrict__ prod) {
     static_assert(!COMBINE || (WANT_DX && !WANT_DV), "combining is for the dx scatter alone");
     constexpr int W = BLOCK * ITEMS;
     // a power of two >= 2W, at most 4096
@@ -63,7 +64,7 @@ __global__ __launch_bounds__(BLOCK) void merge_backward_kernel(
         const int32_t jk = j0 + k;
         re[u] = ro[rk < re_last ? rk : re_last];
         cc[u] = ld_stream(ci + (jk < nz_last ? jk : nz_last));
-        if constexpr (WANT_DX) vv[u] = ld_stream(val + (jk < nz_last ? jk : nz_last));
+        if constexpr (WANT_DX || WANT_PROD) vv[u] = ld_stream(val + (jk < nz_last ? jk : nz_last));
     }
 #pragma unroll
     for (int u = 0; u < ITEMS; ++u) {
@@ -136,6 +137,7 @@ __global__ __launch_bounds__(BLOCK) void merge_backward_kernel(
         if (k < nnzs) {
             const int64_t j = static_cast<int64_t>(j0) + k;
             if constexpr (WANT_DV) dvalues[j] = g[u] * xv[u];
+            if constexpr (WANT_PROD) prod[j] = to_f32(vv[u]) * g[u];
             if constexpr (WANT_DX) unsafeAtomicAdd(dx + cc[u], to_f32(vv[u]) * g[u]);
         }
     }
@@ -143,7 +145,7 @@ __global__ __launch_bounds__(BLOCK) void merge_backward_kernel(
 
 template <int BLOCK, int ITEMS, typename VT>
 static hipError_t run_backward(const csr_dev &A, const void *x, const float *dy, float *dx, float *dvalues, void *ws,
-                               hipStream_t s, bool combine) {
+                               hipStream_t s, bool combine, float *prod) {
     constexpr int W = BLOCK * ITEMS;
     const int64_t T = merge_units(A.rows, A.nnz, W);
     merge_ws w = merge_ws_carve(ws, T);
@@ -153,27 +155,31 @@ static hipError_t run_backward(const csr_dev &A, const void *x, const float *dy,
     const dim3 g(static_cast<uint32_t>(T));
     const VT *xv = static_cast<const VT *>(x);
     const VT *vv = static_cast<const VT *>(A.val);
-    if (dx && !dvalues && combine)
+    if (prod && dvalues)
+        hipLaunchKernelGGL((merge_backward_kernel<BLOCK, ITEMS, VT, false, true, false, true>), g, dim3(BLOCK), 0, s,
+                           A.rows, A.nnz, A.ro, A.ci, vv, xv, dy, dx, dvalues, w.part_i, w.part_j, prod);
+    else if (dx && !dvalues && combine)
         hipLaunchKernelGGL((merge_backward_kernel<BLOCK, ITEMS, VT, true, false, true>), g, dim3(BLOCK), 0, s, A.rows,
-                           A.nnz, A.ro, A.ci, vv, xv, dy, dx, dvalues, w.part_i, w.part_j);
+                           A.nnz, A.ro, A.ci, vv, xv, dy, dx, dvalues, w.part_i, w.part_j, nullptr);
     else if (dx && dvalues)
         hipLaunchKernelGGL((merge_backward_kernel<BLOCK, ITEMS, VT, true, true>), g, dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, vv,
-                           xv, dy, dx, dvalues, w.part_i, w.part_j);
+                           xv, dy, dx, dvalues, w.part_i, w.part_j, nullptr);
     else if (dx)
         hipLaunchKernelGGL((merge_backward_kernel<BLOCK, ITEMS, VT, true, false>), g, dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci,
-                           vv, xv, dy, dx, dvalues, w.part_i, w.part_j);
+                           vv, xv, dy, dx, dvalues, w.part_i, w.part_j, nullptr);
     else
         hipLaunchKernelGGL((merge_backward_kernel<BLOCK, ITEMS, VT, false, true>), g, dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci,
-                           vv, xv, dy, dx, dvalues, w.part_i, w.part_j);
+                           vv, xv, dy, dx, dvalues, w.part_i, w.part_j, nullptr);
     return hipGetLastError();
 }
 
 hipError_t merge_backward(const csr_dev &A, const void *x, const float *dy, float *dx, float *dvalues, int block,
-                          int items, void *ws, hipStream_t s, bool combine_dx) {
+                          int items, void *ws, hipStream_t s, bool combine_dx, float *prod) {
+    if (prod && (dx || !dvalues)) return hipErrorInvalidValue;
 #define X_(B, I)                                                                                             \
     if (block == B && items == I) {                                                                          \
-        if (A.dt == LB_BF16) return run_backward<B, I, bf16_bits>(A, x, dy, dx, dvalues, ws, s, combine_dx); \
-        return run_backward<B, I, float>(A, x, dy, dx, dvalues, ws, s, combine_dx);                          \
+        if (A.dt == LB_BF16) return run_backward<B, I, bf16_bits>(A, x, dy, dx, dvalues, ws, s, combine_dx, prod); \
+        return run_backward<B, I, float>(A, x, dy, dx, dvalues, ws, s, combine_dx, prod);                          \
     }
     LB_MERGE_CONFIGS(X_)
 #undef X_

@@ -104,9 +104,17 @@ hipError_t merge_partition(const int32_t *ro, int32_t rows, int32_t nnz, int32_t
 // (b mod 8) mod 2 of unit (b / 8) * 4 + (b mod 8) / 2, the grid has
 // 8 * ceil(T / 4) blocks and those past the last unit return at once; every
 // (unit, band) pair has exactly one block whatever the hardware's dealing.
-// VPERM (one band only): nonzero j's value is val[vperm[j]], gathered in the
-// same setup as x (the backward's SpMV on A^T reads A's values through the
-// transposed pattern's permutation without a permuted copy).
+// VPERM (one band only; the backward's SpMV on A^T, which reads A's entries
+// through the transposed pattern's permutation without a permuted copy):
+//   1: nonzero j's value is val[vperm[j]], gathered in the same setup as x;
+//   2: nonzero j's product is val[vperm[j]] (a float, formed in A's order), so
+//      one gather per nonzero is left and neither columns nor x are read.
+// Both are bound by their gathers' requests (55M L2 requests in 350 us for 30.8M
+// nonzeros with form 1).  Their blocks take the units in XCD order, block b unit
+// (b mod 8) * ceil(T / 8) + b / 8: the entries of a long row of A that
+// neighbouring columns hold share lines, and those columns' units share an L2
+// (17.9M misses without, 11.8M with it; 373 / 350 us).  The forward's gathers
+// from a 4 MB x measured slower so (156 / 165 us).
 // VEC = 4 (one band, no VPERM): each lane loads four consecutive nonzeros
 // with one 16-byte column load and one 16- (float) or 8-byte (BF16) value
 // load, from groups aligned to 4 in the arrays, so a lane has four times
@@ -129,7 +137,7 @@ hipError_t merge_partition(const int32_t *ro, int32_t rows, int32_t nnz, int32_t
 // [ja, jb).  With units == nullptr (a small one-band lb_spmv, no plan) the
 // block finds its unit's split itself, every unit is launched, and no row
 // is treated as long.
-template <int BLOCK, int ITEMS, typename VT, typename XT, int BANDS, bool VPERM = false, int VEC = 1,
+template <int BLOCK, int ITEMS, typename VT, typename XT, int BANDS, int VPERM = 0, int VEC = 1,
           bool PLAN = false>
 __global__ __launch_bounds__(BLOCK) void merge_spmv_consume(
     int32_t rows, int32_t nnz, const int32_t *__restrict__ ro, const int32_t *__restrict__ ci, const VT *__restrict__ val,
@@ -154,6 +162,9 @@ __global__ __launch_bounds__(BLOCK) void merge_spmv_consume(
         b = static_cast<int>(blockIdx.x / kXcds) * (kXcds / 2) + xcd / 2;
         if (b >= T) return;  // uniform across the block, before any barrier
         if (band == 1) y = y_hi;
+    } else if constexpr (VPERM != 0) {
+        b = static_cast<int>(blockIdx.x % kXcds) * ((T + kXcds - 1) / kXcds) + static_cast<int>(blockIdx.x / kXcds);
+        if (b >= T) return;  // uniform
     }
     // the unit's split; planned: its record (one load), which also gives
     // [ja, jb), the nonzeros whose products this block sums, row i0's head
@@ -275,7 +286,7 @@ __global__ __launch_bounds__(BLOCK) void merge_spmv_consume(
             const int32_t jk = j0 + k;
             const int32_t jc = jk < nz_first ? nz_first : (jk < nz_last ? jk : nz_last);
             re[u] = ro[rk < re_last ? rk : re_last];
-            c[u] = ld_stream(ci + jc);
+            if constexpr (VPERM != 2) c[u] = ld_stream(ci + jc);
             if constexpr (VPERM)
                 vp[u] = ld_stream(vperm + jc);
             else
@@ -285,11 +296,14 @@ __global__ __launch_bounds__(BLOCK) void merge_spmv_consume(
 #pragma unroll
         for (int u = 0; u < ITEMS; ++u) {
             if constexpr (VPERM) v[u] = val[vp[u]];
-            xv[u] = to_f32(x[c[u]]);
+            if constexpr (VPERM != 2) xv[u] = to_f32(x[c[u]]);
         }
 #pragma unroll
         for (int u = 0; u < ITEMS; ++u) {
-            pv[u] = to_f32(v[u]) * xv[u];
+            if constexpr (VPERM == 2)
+                pv[u] = v[u];
+            else
+                pv[u] = to_f32(v[u]) * xv[u];
             if constexpr (PLAN) {
                 const int32_t jk = j0 + tid + u * BLOCK;
                 if (jk < ja || jk >= jb) pv[u] = 0.f;
@@ -526,7 +540,7 @@ static bool vector_loads_ok(const csr_dev &A) {
 
 template <int BLOCK, int ITEMS, typename VT>
 static hipError_t run_merge_spmv(const csr_dev &A, const void *x, float *y, int bands, const int32_t *vperm, int vec,
-                                 void *ws, hipStream_t s) {
+                                 const float *prod, void *ws, hipStream_t s) {
     constexpr int W = BLOCK * ITEMS;
     const int64_t T = merge_units(A.rows, A.nnz, W);
     const bool two = bands == 2;
@@ -538,12 +552,12 @@ static hipError_t run_merge_spmv(const csr_dev &A, const void *x, float *y, int 
         const VT *val = static_cast<const VT *>(A.val);
         const int32_t cb = static_cast<int32_t>((A.cols + 1) / 2);
         if (vec == 4 && vector_loads_ok(A))
-            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 1, false, 4, true>),
+            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 1, 0, 4, true>),
                                dim3(static_cast<uint32_t>(T)), dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, val,
                                static_cast<const VT *>(x), y, nullptr, nullptr, nullptr, nullptr,
                                static_cast<int32_t>(T), cb, nullptr, nullptr, nullptr);
         else
-            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 1, false, 1, true>),
+            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 1, 0, 1, true>),
                                dim3(static_cast<uint32_t>(T)), dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, val,
                                static_cast<const VT *>(x), y, nullptr, nullptr, nullptr, nullptr,
                                static_cast<int32_t>(T), cb, nullptr, nullptr, nullptr);
@@ -555,12 +569,16 @@ static hipError_t run_merge_spmv(const csr_dev &A, const void *x, float *y, int 
         prof_scope p(s, "merge_consume");
         const VT *val = static_cast<const VT *>(A.val);
         const int32_t cb = static_cast<int32_t>((A.cols + 1) / 2);
-        if (vperm) {  // x is float32 (the backward's dy) whatever the value type
-            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, float, 1, true>), dim3(static_cast<uint32_t>(T)),
-                               dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, val, static_cast<const float *>(x), y,
+        const dim3 xcd_grid(static_cast<uint32_t>((T + kXcds - 1) / kXcds * kXcds));
+        if (prod) {
+            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, float, float, 1, 2>), xcd_grid, dim3(BLOCK), 0, s,
+                               A.rows, A.nnz, A.ro, A.ci, prod, nullptr, y, w.part_i, w.part_j, w.carry_row,
+                               w.carry_val, static_cast<int32_t>(T), cb, y_hi, vperm);
+        } else if (vperm) {  // x is float32 (the backward's dy) whatever the value type
+            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, float, 1, 1>), xcd_grid, dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, val, static_cast<const float *>(x), y,
                                w.part_i, w.part_j, w.carry_row, w.carry_val, static_cast<int32_t>(T), cb, y_hi, vperm);
         } else if (vec == 4 && vector_loads_ok(A)) {
-            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 1, false, 4>), dim3(static_cast<uint32_t>(T)),
+            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 1, 0, 4>), dim3(static_cast<uint32_t>(T)),
                                dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, val, static_cast<const VT *>(x), y,
                                w.part_i, w.part_j, w.carry_row, w.carry_val, static_cast<int32_t>(T), cb, y_hi,
                                nullptr);
@@ -600,15 +618,15 @@ static hipError_t run_planned_consume(const csr_dev &A, const plan_dev &pl, cons
     if (pl.bands == 2) {
         const int64_t per = kXcds / 2;
         const int64_t grid = (pl.NA + per - 1) / per * kXcds;
-        hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 2, false, 1, true>),
+        hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 2, 0, 1, true>),
                            dim3(static_cast<uint32_t>(grid)), dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, val, xx, y,
                            pl.part_i, pl.part_j, nullptr, nullptr, pl.NA, cb, y_hi, nullptr, pl.units);
     } else if (pl.vec == 4 && vector_loads_ok(A)) {
-        hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 1, false, 4, true>),
+        hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 1, 0, 4, true>),
                            dim3(static_cast<uint32_t>(pl.NA)), dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, val, xx,
                            y, pl.part_i, pl.part_j, nullptr, nullptr, pl.NA, cb, nullptr, nullptr, pl.units);
     } else {
-        hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 1, false, 1, true>),
+        hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 1, 0, 1, true>),
                            dim3(static_cast<uint32_t>(pl.NA)), dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, val, xx,
                            y, pl.part_i, pl.part_j, nullptr, nullptr, pl.NA, cb, nullptr, nullptr, pl.units);
     }
@@ -635,15 +653,15 @@ bool merge_config_supported(int block, int items) {
 }
 
 hipError_t merge_spmv(const csr_dev &A, const void *x, float *y, int block, int items, int bands, void *ws,
-                      hipStream_t s, const int32_t *vperm, int vec) {
+                      hipStream_t s, const int32_t *vperm, int vec, const float *prod) {
     if (bands != 1 && bands != 2) return hipErrorInvalidValue;
     if (vec != 1 && vec != 4) return hipErrorInvalidValue;
     if ((vperm || vec == 4) && bands != 1) return hipErrorInvalidValue;
-    if (vperm && vec != 1) return hipErrorInvalidValue;
+    if ((vperm && vec != 1) || (prod && !vperm)) return hipErrorInvalidValue;
 #define X(B, I)                                                                                     \
     if (block == B && items == I) {                                                                 \
-        if (A.dt == LB_BF16) return run_merge_spmv<B, I, bf16_bits>(A, x, y, bands, vperm, vec, ws, s); \
-        return run_merge_spmv<B, I, float>(A, x, y, bands, vperm, vec, ws, s);                      \
+        if (A.dt == LB_BF16) return run_merge_spmv<B, I, bf16_bits>(A, x, y, bands, vperm, vec, prod, ws, s); \
+        return run_merge_spmv<B, I, float>(A, x, y, bands, vperm, vec, prod, ws, s);                \
     }
     LB_MERGE_CONFIGS(X)
 #undef X

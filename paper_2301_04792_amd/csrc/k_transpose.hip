@@ -2,9 +2,9 @@
 // the transposed pattern.  A training loop keeps one sparsity pattern across
 // steps, so the transpose is built once (transpose_pattern) and each
 // backward runs the forward's merge-path kernels on A^T, reading the current
-// values of A through the pattern's permutation (val[perm[p]], gathered in
-// the consume kernel's setup); dvalues comes from the backward kernel's
-// dvalues-only pass.
+// products of A's values and dy through the pattern's permutation
+// (prod[perm[p]], gathered in the consume kernel's setup), which the pass over
+// A that gives dvalues forms in A's order.
 //
 // Transpose of a CSR pattern A (rows x cols) without global atomics: a
 // stable least-significant-digit radix sort of the nonzeros by column.
@@ -471,24 +471,40 @@ hipError_t transpose_pattern(const csr_dev &A, int32_t *at_ro, int32_t *at_ci, i
     return hipGetLastError();
 }
 
-size_t backward_transposed_ws_bytes(int64_t rows, int64_t cols, int64_t nnz, int block, int items) {
+// Workspace: the split and carries of one pass at a time, then the products.
+static size_t transposed_split_bytes(int64_t rows, int64_t cols, int64_t nnz, int block, int items) {
     const int64_t W = static_cast<int64_t>(block) * items;
-    const size_t a = merge_ws_bytes(merge_units(rows, nnz, W), 1);  // dvalues pass over A
+    const size_t a = merge_ws_bytes(merge_units(rows, nnz, W), 1);  // the pass over A
     const size_t b = merge_ws_bytes(merge_units(cols, nnz, W), 1);  // SpMV over A^T
     return a > b ? a : b;
 }
 
+size_t backward_transposed_ws_bytes(int64_t rows, int64_t cols, int64_t nnz, int block, int items, bool products) {
+    return transposed_split_bytes(rows, cols, nnz, block, items) +
+           (products ? align256(static_cast<size_t>(nnz) * 4) : 0);
+}
+
 hipError_t backward_transposed(const csr_dev &A, const int32_t *at_ro, const int32_t *at_ci, const int32_t *perm,
                                const void *x, const float *dy, float *dx, float *dvalues, int block, int items,
-                               void *ws, hipStream_t s) {
+                               void *ws, bool products, hipStream_t s) {
+    // The pass over A that dvalues needs also leaves the products, so that the
+    // SpMV on A^T gathers one word a nonzero instead of two (values and dy): 1M
+    // power-law rows, 31.6M nonzeros, both gradients 497 -> 383 us; a stencil of
+    // 5.2M 49.1 / 50.8.  Without dvalues the pass would come on top (the stencil's
+    // dx alone 29.2 / 45.0, 1.6M power-law 27.2 / 33.8, 31.6M 342 / 229), so dx
+    // alone gathers both.
+    float *prod = nullptr;
+    if (products && dx && dvalues)
+        prod = reinterpret_cast<float *>(static_cast<char *>(ws) +
+                                         transposed_split_bytes(A.rows, A.cols, A.nnz, block, items));
     if (dvalues) {
-        const hipError_t e = merge_backward(A, x, dy, nullptr, dvalues, block, items, ws, s);
+        const hipError_t e = merge_backward(A, x, dy, nullptr, dvalues, block, items, ws, s, false, prod);
         if (e != hipSuccess) return e;
     }
     if (!dx) return hipSuccess;
     // A^T with A's values (of A's type) read through perm; x of this SpMV is dy
     const csr_dev AT{A.cols, A.rows, A.nnz, at_ro, at_ci, A.val, A.dt};
-    return merge_spmv(AT, dy, dx, block, items, 1, ws, s, perm);
+    return merge_spmv(AT, dy, dx, block, items, 1, ws, s, perm, 1, prod);
 }
 
 }  // namespace lbk

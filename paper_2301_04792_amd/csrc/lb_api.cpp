@@ -1173,7 +1173,8 @@ LB_API lb_status_t lb_backward_transposed_workspace_size(const lb_csr_t *A, cons
     lb_schedule_t r;
     st = backward_transposed_schedule(s, &r);
     if (st != LB_OK) return st;
-    *bytes = lbk::backward_transposed_ws_bytes(A->rows, A->cols, A->nnz, r.block_size, r.items_per_thread);
+    *bytes = lbk::backward_transposed_ws_bytes(A->rows, A->cols, A->nnz, r.block_size, r.items_per_thread,
+                                               A->nnz >= lbk::kProductsMinNnz);
     return LB_OK;
 }
 
@@ -1182,23 +1183,27 @@ LB_API lb_status_t lb_spmv_backward_transposed(const lb_csr_t *A, const int32_t 
                                                lb_dtype_t x_dtype, const float *dy, float *dx, float *dvalues,
                                                const lb_schedule_t *s, void *workspace, size_t workspace_bytes,
                                                void *stream) {
-    size_t need = 0;
-    lb_status_t st = lb_backward_transposed_workspace_size(A, s, &need);
+    size_t full = 0;
+    lb_status_t st = lb_backward_transposed_workspace_size(A, s, &full);
     if (st != LB_OK) return st;
     if (x_dtype != A->value_dtype) return LB_ERR_UNSUPPORTED;
     if (A->rows > 0 && A->nnz > 0 && !dy && (dx || dvalues)) return LB_ERR_INVALID_ARG;
     if (dvalues && A->nnz > 0 && !x) return LB_ERR_INVALID_ARG;
     if (dx && (!at_row_offsets || (A->nnz > 0 && (!at_col_idx || !perm)))) return LB_ERR_INVALID_ARG;
-    if (!workspace || workspace_bytes < need) return LB_ERR_WORKSPACE_TOO_SMALL;
     lb_schedule_t r;
     (void)backward_transposed_schedule(s, &r);
+    // a workspace without room for the products gathers A's values and dy instead
+    const size_t need =
+        lbk::backward_transposed_ws_bytes(A->rows, A->cols, A->nnz, r.block_size, r.items_per_thread, false);
+    if (!workspace || workspace_bytes < need) return LB_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     if (A->nnz == 0 || A->rows == 0) {  // no entries: dx = 0, no dvalues
         if (dx && A->cols > 0) return hip_status(lbk::fill_f32(dx, A->cols, 0.f, hs));
         return LB_OK;
     }
     return hip_status(lbk::backward_transposed(to_dev(A), at_row_offsets, at_col_idx, perm, x, dy, dx, dvalues,
-                                               r.block_size, r.items_per_thread, workspace, hs));
+                                               r.block_size, r.items_per_thread, workspace,
+                                               A->nnz >= lbk::kProductsMinNnz && workspace_bytes >= full, hs));
 }
 
 lb_status_t check_spgemm(const lb_csr_t *A, const lb_csr_t *B) {

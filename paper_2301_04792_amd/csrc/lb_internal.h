@@ -100,12 +100,13 @@ hipError_t launch_fixup(int64_t T, int32_t rows, int32_t kc, const int32_t *carr
 
 // bands 1 or 2 (column bands of x, one per half of the XCDs); the workspace
 // is merge_ws_bytes(T, 1) for one band, merge_banded_ws_bytes(T, rows) for two.
-// With vperm (one band), nonzero j's value is A.val[vperm[j]] and x is float32.
+// With vperm (one band), nonzero j's value is A.val[vperm[j]] and x is float32;
+// with prod too, its product is prod[vperm[j]] and x, A.ci and A.val are not read.
 // vec 4 (one band, no vperm): four consecutive nonzeros per lane and load;
 // the one-nonzero form runs instead when nnz < 4 or col_idx / values are
 // not aligned to their vectors.
 hipError_t merge_spmv(const csr_dev &A, const void *x, float *y, int block, int items, int bands, void *ws,
-                      hipStream_t s, const int32_t *vperm = nullptr, int vec = 1);
+                      hipStream_t s, const int32_t *vperm = nullptr, int vec = 1, const float *prod = nullptr);
 
 // ---- planned SpMV (k_plan.hip) ----------------------------------------------------------
 // Long rows: a block of kPanelBlock threads stages kPanelBytes of x (one
@@ -226,8 +227,10 @@ hipError_t merge_spmm(const csr_dev &A, const void *X, int32_t k, int64_t ldx, f
 
 // combine_dx (dx only): products are summed per target in LDS before the
 // global atomics (for scatters whose targets repeat within a unit).
+// prod (with dvalues, without dx): the products values[j] * dy[row(j)], nnz floats.
 hipError_t merge_backward(const csr_dev &A, const void *x, const float *dy, float *dx, float *dvalues,
-                          int block, int items, void *ws, hipStream_t s, bool combine_dx = false);
+                          int block, int items, void *ws, hipStream_t s, bool combine_dx = false,
+                          float *prod = nullptr);
 
 // ---- the backward's scatter by bins (k_bins.hip) ----------------------------------------
 // Whether dx (A.cols targets, written whole) is summed by bins.  us, by bins and
@@ -277,11 +280,15 @@ size_t transpose_ws_bytes(int64_t cols, int64_t nnz);
 // A^T's offsets (cols + 1), column indices (= rows of A) and the A entry of each A^T entry.
 hipError_t transpose_pattern(const csr_dev &A, int32_t *at_ro, int32_t *at_ci, int32_t *perm, void *ws,
                              hipStream_t s);
-size_t backward_transposed_ws_bytes(int64_t rows, int64_t cols, int64_t nnz, int block, int items);
-// dvalues (dvalues-only merge pass over A) and dx = A^T dy (merge-path SpMV on A^T reading A's values through perm).
+// products: with room for the nonzeros' products, for at least kProductsMinNnz
+// (fewer stay in the caches either way: 0.37M nonzeros 21.1 / 21.6 us).
+constexpr int64_t kProductsMinNnz = 1000000;
+size_t backward_transposed_ws_bytes(int64_t rows, int64_t cols, int64_t nnz, int block, int items, bool products);
+// dvalues (merge pass over A) and dx = A^T dy (merge-path SpMV on A^T, reading through perm the products that
+// the pass over A left in the workspace or, without room for them, A's values).
 hipError_t backward_transposed(const csr_dev &A, const int32_t *at_ro, const int32_t *at_ci, const int32_t *perm,
                                const void *x, const float *dy, float *dx, float *dvalues, int block, int items,
-                               void *ws, hipStream_t s);
+                               void *ws, bool products, hipStream_t s);
 
 // ---- SpGEMM (k_spgemm.hip) ---------------------------------------------------------------
 // C = A B with A m x k and B k x n (float32 values).
