@@ -7,8 +7,8 @@
 // of the selected B row, which ranges from a few to millions on power-law
 // inputs.  Rows are sorted into four tiers by p_i, each with its own
 // accumulator:
-//   tier 0 (p_i <= 32):    an 8-lane group per row, the same with a fixed
-//                           32-element network, eight rows per wavefront;
+//   tier 0 (p_i <= 32):    an 8-lane group per row, eight rows per wavefront,
+//                           sorted in registers;
 //   tier 1 (p_i <= 256):   one wavefront per row; the products, keyed by
 //                           (column, product index), are bitonic-sorted in
 //                           the wavefront's LDS; equal columns are then
@@ -36,6 +36,7 @@ using namespace lb;
 namespace {
 
 constexpr int kTier0 = 32;  // an 8-lane group per row, 8 rows per wavefront
+constexpr int kTier0Bits = 27;  // C's columns fit this many bits (wider ones: tier 1)
 constexpr int kTier1 = 256;
 constexpr int kTier2 = 4096;
 constexpr int kBlock = 256;
@@ -138,8 +139,9 @@ __global__ __launch_bounds__(256) void gemm_products(gemm_args g, int64_t *__res
 // matrix whose rows share a tier, ~200 µs of serialized atomics.)
 constexpr int kClassRows = 1024;
 
-__device__ __forceinline__ int gemm_tier_of(int64_t p) {
-    return p < 0 ? -1 : (p <= kTier0 ? 3 : (p <= kTier1 ? 0 : (p <= kTier2 ? 1 : 2)));
+__device__ __forceinline__ int gemm_tier_of(int64_t p, int32_t n) {
+    if (p <= kTier0) return p < 0 ? -1 : (n < (1 << kTier0Bits) ? 3 : 0);
+    return p <= kTier1 ? 0 : (p <= kTier2 ? 1 : 2);
 }
 
 __global__ __launch_bounds__(256) void gemm_classify(gemm_args g) {
@@ -152,7 +154,7 @@ __global__ __launch_bounds__(256) void gemm_classify(gemm_args g) {
     int32_t cnt[4] = {0, 0, 0, 0};
     for (int64_t i0 = r0 + w * kWave; i0 < r1; i0 += 256) {  // uniform per wavefront
         const int64_t i = i0 + lane;
-        const int t = gemm_tier_of(i < r1 ? g.prod[i] : -1);
+        const int t = gemm_tier_of(i < r1 ? g.prod[i] : -1, g.n);
 #pragma unroll
         for (int q = 0; q < 4; ++q) cnt[q] += __popcll(__ballot(t == q));
     }
@@ -174,7 +176,7 @@ __global__ __launch_bounds__(256) void gemm_classify(gemm_args g) {
     }
     for (int64_t i0 = r0 + w * kWave; i0 < r1; i0 += 256) {
         const int64_t i = i0 + lane;
-        const int t = gemm_tier_of(i < r1 ? g.prod[i] : -1);
+        const int t = gemm_tier_of(i < r1 ? g.prod[i] : -1, g.n);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const uint64_t mask = __ballot(t == q);
@@ -214,74 +216,154 @@ __device__ __forceinline__ void lds_bitonic(uint64_t *key, float *val, int32_t n
     }
 }
 
-// Tier 0: an 8-lane group per row (p <= 32), eight rows per wavefront; all
-// groups run the same 32-element sort network, so the wavefront stays in
-// step (a group whose rows ran out is masked off).
+// Exchange with lane gl ^ D of an aligned group of eight lanes (DPP: no LDS).
+template <int D>
+__device__ __forceinline__ uint32_t swap8(uint32_t v) {
+    static_assert(D == 1 || D == 2 || D == 4, "lane distances in eight lanes");
+    auto dpp = [](uint32_t x, auto ctrl) {
+        return static_cast<uint32_t>(
+            __builtin_amdgcn_update_dpp(0, static_cast<int>(x), decltype(ctrl)::value, 0xF, 0xF, false));
+    };
+    if constexpr (D == 1) return dpp(v, std::integral_constant<int, 0xB1>{});  // quad_perm [1,0,3,2]
+    if constexpr (D == 2) return dpp(v, std::integral_constant<int, 0x4E>{});  // quad_perm [2,3,0,1]
+    // half-row mirror (gl ^ 7), then quad_perm [3,2,1,0] (gl ^ 3)
+    return dpp(dpp(v, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{});
+}
+
+// Ascending bitonic sort of 32 keys held by eight lanes, lane gl elements
+// 4 gl .. 4 gl + 3: distances 1 and 2 are inside a lane, 4, 8 and 16 are lane
+// exchanges.
+__device__ __forceinline__ void sort32(uint32_t (&k)[4], int gl) {
+    auto pair = [](uint32_t &x, uint32_t &y, bool up) {
+        const uint32_t lo = x < y ? x : y, hi = x < y ? y : x;
+        x = up ? lo : hi;
+        y = up ? hi : lo;
+    };
+    auto inside = [&](bool up) {  // distances 2, then 1
+        pair(k[0], k[2], up), pair(k[1], k[3], up);
+        pair(k[0], k[1], up), pair(k[2], k[3], up);
+    };
+    auto across = [&](auto dist, bool up) {
+        constexpr int D = decltype(dist)::value;
+        const bool keep_min = ((gl & D) == 0) == up;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t o = swap8<D>(k[r]);
+            const uint32_t lo = k[r] < o ? k[r] : o, hi = k[r] < o ? o : k[r];
+            k[r] = keep_min ? lo : hi;
+        }
+    };
+    using d1 = std::integral_constant<int, 1>;
+    using d2 = std::integral_constant<int, 2>;
+    using d4 = std::integral_constant<int, 4>;
+    pair(k[0], k[1], true), pair(k[2], k[3], false);
+    inside((gl & 1) == 0);
+    const bool up8 = (gl & 2) == 0, up16 = (gl & 4) == 0;
+    across(d1{}, up8), inside(up8);
+    across(d2{}, up16), across(d1{}, up16), inside(up16);
+    across(d4{}, true), across(d2{}, true), across(d1{}, true), inside(true);
+}
+
+// Tier 0: an 8-lane group per row (p <= 32), eight rows per wavefront.  The
+// products are expanded into LDS and sorted in registers, four per lane, by one
+// 32-bit key (column, product index), so n < 2^kTier0Bits; a value is fetched
+// by its product index once its place is known.  (A 32-element network of
+// 64-bit keys and values in LDS took 234 us for the count and 443 for the
+// compute pass of the 1024 x 1024 stencil squared, 26.2M products.)
 template <bool COMPUTE>
 __global__ __launch_bounds__(kBlock) void gemm_tier0(gemm_args g) {
     constexpr int GL = 8;
     constexpr int GPB = kBlock / GL;
-    __shared__ uint64_t s_key[GPB][kTier0];
-    __shared__ float s_val[GPB][COMPUTE ? kTier0 : 1];
+    constexpr int STRIDE = kTier0 + 4;  // 16-byte rows whose starts spread over the banks
+    __shared__ __align__(16) uint32_t s_key[GPB][STRIDE];
+    __shared__ float s_val[GPB][COMPUTE ? STRIDE : 1];
     const int gl = threadIdx.x & (GL - 1), gi = threadIdx.x / GL;
-    const int shift = lane_id() & ~(GL - 1);  // the group's first lane in the wavefront
-    uint64_t *key = s_key[gi];
+    uint32_t *key = s_key[gi];
     float *val = s_val[gi];
     const int32_t rows = g.list_len[4];
     const int64_t groups = static_cast<int64_t>(gridDim.x) * GPB;
     for (int64_t r = static_cast<int64_t>(blockIdx.x) * GPB + gi; r < rows; r += groups) {
         const int32_t i = g.lists[3 * static_cast<int64_t>(g.m) + r];
-        const int32_t p = static_cast<int32_t>(g.prod[i]);
         const int32_t a0 = g.a_ro[i], a1 = g.a_ro[i + 1];
-        int32_t base = 0;
-        for (int32_t c0 = a0; c0 < a1; c0 += GL) {
+        const int32_t out0 = COMPUTE ? g.c_ro[i] : 0;
+        int32_t p = 0;
+        for (int32_t c0 = a0; c0 < a1; c0 += GL) {  // uniform over the group
             const int32_t e = c0 + gl;
-            int32_t j = 0, len = 0;
+            int32_t f0 = 0, len = 0;
+            float a = 0.f;
             if (e < a1) {
-                j = g.a_ci[e];
-                len = g.b_ro[j + 1] - g.b_ro[j];
+                const int32_t j = g.a_ci[e];
+                if constexpr (COMPUTE) a = g.a_val[e];
+                f0 = g.b_ro[j];
+                len = g.b_ro[j + 1] - f0;
             }
             const int32_t incl = group_scan_incl<GL>(len);
-            const int32_t start = base + incl - len;
-            if (len > 0) {
-                const int32_t f0 = g.b_ro[j];
-                const float a = COMPUTE ? g.a_val[e] : 0.f;
-                for (int32_t t = 0; t < len; ++t) {
-                    const int32_t q = start + t;
-                    key[q] = (static_cast<uint64_t>(g.b_ci[f0 + t]) << 32) | static_cast<uint32_t>(q);
-                    if constexpr (COMPUTE) val[q] = a * g.b_val[f0 + t];
+            const int32_t start = p + incl - len;
+            constexpr int U = 6;  // loads in flight per lane
+            for (int32_t t0 = 0; t0 < len; t0 += U) {
+                int32_t c[U];
+                float b[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int32_t f = f0 + (t0 + u < len ? t0 + u : len - 1);
+                    c[u] = g.b_ci[f];
+                    if constexpr (COMPUTE) b[u] = g.b_val[f];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int32_t q = start + t0 + u;
+                    if (t0 + u < len) {
+                        key[q] = (static_cast<uint32_t>(c[u]) << 5) | static_cast<uint32_t>(q);
+                        if constexpr (COMPUTE) val[q] = a * b[u];
+                    }
                 }
             }
-            base += __shfl(incl, GL - 1, GL);
+            p += __shfl(incl, GL - 1, GL);
         }
-        for (int32_t q = p + gl; q < kTier0; q += GL) key[q] = kPad;
+        for (int32_t q = p + gl; q < kTier0; q += GL) key[q] = 0xffffffffu;  // sorts after every real key
         wave_sync();
-        lds_bitonic<COMPUTE>(key, val, kTier0, gl, GL, wave_sync);
-        int32_t rank = 0;
-        float carry = 0.f;
-        const int32_t out0 = COMPUTE ? g.c_ro[i] : 0;
-        for (int32_t c0 = 0; c0 < p; c0 += GL) {
-            const int32_t q = c0 + gl;
-            const bool in = q < p;
-            const uint32_t col = in ? static_cast<uint32_t>(key[q] >> 32) : 0xffffffffu;
-            const uint32_t prev = q > 0 && in ? static_cast<uint32_t>(key[q - 1] >> 32) : 0xffffffffu;
-            const bool head = in && (q == 0 || col != prev);
-            const uint32_t hm = static_cast<uint32_t>((__ballot(head) >> shift) & 0xffu);
-            if constexpr (COMPUTE) {
-                const bool tail = in && (q == p - 1 || static_cast<uint32_t>(key[q + 1] >> 32) != col);
-                seg_t sv = group_seg_scan_incl<GL>(seg_t{in ? val[q] : 0.f, head});
-                if (!sv.f) sv.v += carry;
-                const int32_t my_rank = rank + __popc(hm & ((2u << gl) - 1)) - 1;
-                if (tail) {
-                    g.c_ci[out0 + my_rank] = static_cast<int32_t>(col);
-                    g.c_val[out0 + my_rank] = sv.v;
-                }
-                carry = __shfl(sv.v, GL - 1, GL);
-            }
-            rank += __popc(hm);
+        uint32_t k[4];
+        {
+            const uint4 k4 = *reinterpret_cast<const uint4 *>(key + 4 * gl);
+            k[0] = k4.x, k[1] = k4.y, k[2] = k4.z, k[3] = k4.w;
         }
-        if constexpr (!COMPUTE) {
-            if (gl == 0) g.c_ro[i] = rank;
+        sort32(k, gl);
+        // heads of the runs of equal columns among the first p elements
+        const uint32_t before = static_cast<uint32_t>(__shfl_up(static_cast<int>(k[3]), 1, GL));
+        bool head[4];
+        int32_t cnt = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t last = q ? k[q - 1] : before;
+            head[q] = 4 * gl + q < p && ((q == 0 && gl == 0) || (k[q] >> 5) != (last >> 5));
+            cnt += head[q] ? 1 : 0;
+        }
+        const int32_t upto = group_scan_incl<GL>(cnt);
+        if constexpr (COMPUTE) {
+            float v[4];
+            seg_t mine{0.f, 0};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                v[q] = 4 * gl + q < p ? val[k[q] & (kTier0 - 1)] : 0.f;
+                mine = head[q] ? seg_t{v[q], 1} : seg_t{mine.v + v[q], mine.f};
+            }
+            const seg_t incl = group_seg_scan_incl<GL>(mine);
+            const float open = __shfl_up(incl.v, 1, GL);
+            const int after = __shfl_down(static_cast<int>(head[0]), 1, GL);  // the next lane starts a run
+            float sum = gl ? open : 0.f;
+            int32_t at = out0 + upto - cnt - 1;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                sum = head[q] ? v[q] : sum + v[q];
+                at += head[q] ? 1 : 0;
+                const bool next = q < 3 ? head[q < 3 ? q + 1 : 3] : (after != 0 && gl < GL - 1);
+                if (4 * gl + q < p && (next || 4 * gl + q == p - 1)) {
+                    g.c_ci[at] = static_cast<int32_t>(k[q] >> 5);
+                    g.c_val[at] = sum;
+                }
+            }
+        } else {
+            if (gl == GL - 1) g.c_ro[i] = upto;
         }
         wave_sync();
     }
@@ -438,6 +520,19 @@ __global__ __launch_bounds__(kBlock) void gemm_tier2(gemm_args g) {
 
 // ---------------------------------------------------------------- tier 3: dense slot per block
 
+// The slots that gemm_tier3 will use start clear (it clears what it used): as
+// many as there are rows, up to `slots`.  Clearing all of them took 190 us (1 GiB
+// of sums at n = 1M) where no row was this large.
+template <bool COMPUTE>
+__global__ __launch_bounds__(256) void gemm_clear_slots(gemm_args g, int64_t slots) {
+    const int64_t used = g.list_len[2] < slots ? g.list_len[2] : slots;
+    for (int64_t q : grid_stride_range(0, used * g.slot_words)) g.slot_bits[q] = 0u;
+    if constexpr (COMPUTE)
+        for (int64_t q : grid_stride_range(0, used * g.n)) g.slot_acc[q] = 0.f;
+}
+
+// A block per slot; a block past the rows leaves, so the slots that the queue's
+// rows use are the first ones.
 template <bool COMPUTE>
 __global__ __launch_bounds__(kBlock) void gemm_tier3(gemm_args g) {
     using sched = group_mapped_scan<kBlock, indexed_tile_set>;
@@ -446,6 +541,7 @@ __global__ __launch_bounds__(kBlock) void gemm_tier3(gemm_args g) {
     __shared__ int32_t s_slot;
     __shared__ int32_t s_int;
     const int tid = threadIdx.x;
+    if (static_cast<int32_t>(blockIdx.x) >= g.list_len[2]) return;  // uniform
     const int64_t nw0 = (static_cast<int64_t>(g.n) + 31) / 32;  // level-0 words: a bit per column
     float *acc = g.slot_acc + static_cast<int64_t>(blockIdx.x) * g.n;
     uint32_t *bits = g.slot_bits + static_cast<int64_t>(blockIdx.x) * g.slot_words;
@@ -555,16 +651,35 @@ __global__ __launch_bounds__(256) void gemm_scan_tiles(const int32_t *__restrict
     if (threadIdx.x == 255) tile_sum[blockIdx.x] = incl;
 }
 
-// One thread: exclusive prefix of the tile totals (few: m / 2048) and the grand total.
-__global__ void gemm_scan_totals(int64_t *__restrict__ tile_sum, int64_t nb, int64_t *__restrict__ total) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    int64_t run = 0;
-    for (int64_t b = 0; b < nb; ++b) {
-        const int64_t t = tile_sum[b];
-        tile_sum[b] = run;
-        run += t;
+// One block: exclusive prefix of the tile totals (m / 2048 of them) and the
+// grand total (one thread took 60 us for 513 tiles).
+constexpr int kTotalsBlock = 1024;
+__global__ __launch_bounds__(kTotalsBlock) void gemm_scan_totals(int64_t *__restrict__ tile_sum, int64_t nb,
+                                                                 int64_t *__restrict__ total) {
+    __shared__ int64_t s_w[kTotalsBlock / kWave];
+    int64_t carry = 0;
+    for (int64_t b0 = 0; b0 < nb; b0 += kTotalsBlock) {  // uniform across the block
+        const int64_t b = b0 + threadIdx.x;
+        const int64_t v = b < nb ? tile_sum[b] : 0;
+        int64_t incl = v;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int64_t o = __shfl_up(incl, off, kWave);
+            if (lane_id() >= off) incl += o;
+        }
+        if (lane_id() == kWave - 1) s_w[wave_id()] = incl;
+        __syncthreads();
+        int64_t sum = 0;
+#pragma unroll
+        for (int k = 0; k < kTotalsBlock / kWave; ++k) {
+            if (k < wave_id()) incl += s_w[k];
+            sum += s_w[k];
+        }
+        if (b < nb) tile_sum[b] = carry + incl - v;
+        carry += sum;
+        __syncthreads();
     }
-    *total = run;
+    if (threadIdx.x == 0) *total = carry;
 }
 
 // C's row offsets (int32) where the total fits; the host checks the total first.
@@ -647,11 +762,11 @@ static hipError_t gemm_pass(const spgemm_dev &P, int32_t *c_ro, int32_t *c_ci, f
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    // tier-3 slots start clear (the kernel clears what it used)
     const int64_t slots = spgemm_slots(P.n);
-    e = fill_f32(reinterpret_cast<float *>(w.slot_bits), slots * w.slot_words, 0.f, s);
-    if (e == hipSuccess && compute) e = fill_f32(w.slot_acc, slots * P.n, 0.f, s);
-    if (e != hipSuccess) return e;
+    if (compute)
+        hipLaunchKernelGGL(gemm_clear_slots<true>, dim3(1024), dim3(256), 0, s, g, slots);
+    else
+        hipLaunchKernelGGL(gemm_clear_slots<false>, dim3(256), dim3(256), 0, s, g, slots);
     // one launch per tier (each reads its list's length on the device)
     const uint32_t grid12 = static_cast<uint32_t>(capped(P.m, 1) < 2048 ? capped(P.m, 1) : 2048);
     const char *names[2][4] = {{"spgemm_count_t0", "spgemm_count_t1", "spgemm_count_t2", "spgemm_count_t3"},
@@ -697,7 +812,7 @@ hipError_t spgemm_count(const spgemm_dev &P, int32_t *c_ro, int64_t *total_host,
     if (nb > 0)
         hipLaunchKernelGGL(gemm_scan_tiles, dim3(static_cast<uint32_t>(nb)), dim3(256), 0, s, c_ro,
                            static_cast<int64_t>(P.m), w.pre, w.tile_sum);
-    hipLaunchKernelGGL(gemm_scan_totals, dim3(1), dim3(64), 0, s, w.tile_sum, nb, w.total);
+    hipLaunchKernelGGL(gemm_scan_totals, dim3(1), dim3(kTotalsBlock), 0, s, w.tile_sum, nb, w.total);
     hipLaunchKernelGGL(gemm_scan_write, dim3(static_cast<uint32_t>(capped(P.m, 256))), dim3(256), 0, s, w.pre,
                        w.tile_sum, w.total, static_cast<int64_t>(P.m), c_ro);
     e = hipGetLastError();
