@@ -15,15 +15,13 @@
 //  * BFS: depth is int32, -1 = unvisited; the compare-and-swap from -1 to
 //    i + 1 that succeeds claims the vertex.
 // Appends are aggregated per block: the merge-path advance places a unit's
-// new vertices with a block prefix sum and one atomicAdd; the other
+// new vertices with a block prefix sum and one 64-bit atomicAdd; the other
 // schedules stage them in an LDS buffer and reserve its stretch with one
 // atomicAdd per block (per round for the prefix-sum form).  Pushes past the
 // buffer fall back to one atomicAdd per wavefront.
 //
-// Under merge-path an iteration is five launches (degree scan, split,
-// consume; see below); under the other schedules one.  Each advance launch
-// is persistent (the resident grid) and reads the frontier size from device
-// memory, so the host enqueues a batch of
+// An iteration is one launch, persistent (the resident grid), that reads the
+// frontier size from device memory, so the host enqueues a batch of
 // iterations without waiting and reads the size once per batch to stop.
 // Three rotating counters: launch i reads counter i % 3, appends to
 // (i + 1) % 3 and zeroes (i + 2) % 3, the one launch i + 1 appends to (and
@@ -227,194 +225,246 @@ __global__ __launch_bounds__(group_block<G>::BLOCK) void advance_scan_kernel(tra
 
 // ---------------------------------------------------------------- merge-path over the frontier
 //
-// The frontier as a tile set for merge-path (Sec. 5.2.1) needs its "row
-// offsets": offs[p] = out-degrees of frontier entries [0, p).  Per
-// iteration: (1) per tile of kScanTile entries, the in-tile exclusive
-// prefix sums and the tile total; (2) one block scans the tile totals and
-// records the frontier's edge count E_f and unit count T_f; (3) the tile
-// prefixes are added in; (4) the split at every unit boundary of the merge
-// of offs[1..nf] with the edges 0..E_f-1 (the SpMV split); (5) a persistent
-// consume: each unit stages its frontier entries in LDS and each thread
-// walks kMergeItems merge items, relaxing the edges it meets; the unit's new
-// frontier vertices are appended with one atomic per block (a block prefix
-// sum of the threads' counts), not one per wavefront and merge item.  Every
-// grid is sized for the largest frontier (every vertex); blocks past the
-// frontier's work leave at once.
+// One launch per iteration.  The frontier carries its own "row offsets": the
+// vertices that have out-edges are stored in slots with the exclusive prefix sum
+// of their degrees, because a block reserves its new vertices' slots and edges
+// with one 64-bit atomicAdd (slots in the low word, edges in the high one), so
+// slot order and edge order agree.  Offsets are kept for even slots only (the
+// odd one's is the even one's plus its degree), which fits both frontiers' into
+// n + 1 words.  A vertex without out-edges takes no slot; it only marks the
+// next frontier as non-empty.  A unit is kEdgeUnit consecutive edges of the
+// frontier, whoever owns them: blocks take equal contiguous ranges of units, find
+// the first slot by a search over the offsets, stage the slots of a unit in
+// LDS, and each thread takes kEdgeItems edges strided by the block.  Every load
+// of a kind (targets and weights, then target states, then atomics) is in flight
+// for all of a thread's edges together: a walk of one edge after the other
+// waited for three dependent loads each.  The earlier form's four launches per
+// iteration for the offsets (degree scan in three, split) are gone.  1M-vertex
+// power-law graph, 30.8M edges: BFS 576 -> 365 us, SSSP 2.48 -> 1.55 ms; a
+// 200 x 200 grid, BFS in 335 iterations, 7.2 -> 3.4 ms.  512 x 4 edges: 256 x 8
+// has fewer wavefronts for the LDS a unit takes (396 us, 1.64 ms), 1024 x 2 fewer
+// blocks (504 us, 1.86 ms).  Bound: the random target states (24M in 180 us) and
+// returning atomics, both device-wide.
 
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 8;
-constexpr int kScanTile = kScanThreads * kScanItems;
-constexpr int kMergeBlock = 256;
-constexpr int kMergeItems = 8;
-constexpr int kMergeW = kMergeBlock * kMergeItems;
-constexpr int kPartGroup = 16;
+constexpr int kEdgeBlock = 512;
+constexpr int kEdgeItems = 4;
+constexpr int kEdgeUnit = kEdgeBlock * kEdgeItems;
+// slots staged: a unit overlaps at most kEdgeUnit + 1, after one of its first
+// pair, and pairs are loaded kEdgeBlock at a time
+constexpr int kEdgeSlots = (kEdgeUnit / 2 + 2 + kEdgeBlock - 1) / kEdgeBlock * kEdgeBlock * 2;
 
-__global__ __launch_bounds__(kScanThreads) void frontier_scan_tiles(const int32_t *__restrict__ q,
-                                                                    const int32_t *__restrict__ cnt_in,
-                                                                    const int32_t *__restrict__ ro,
-                                                                    int32_t *__restrict__ offs,
-                                                                    int32_t *__restrict__ tile_sum) {
-    __shared__ int32_t s_wave[kScanThreads / kWave];
-    const int32_t nf = *cnt_in;
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * kScanTile;
-    if (base >= nf) return;  // uniform across the block
-    int32_t deg[kScanItems];
-    int32_t sum = 0;
+// New vertices a block holds before it reserves their slots: with one atomic per
+// unit the blocks of a large iteration queued on the one counter (12k atomics).
+constexpr int kEdgeNew = 2 * kEdgeUnit;
+
+struct edge_args {
+    const int32_t *off_in;  // offset of slot 2t at t
+    int32_t *off_out;
+    const unsigned long long *pk_in;  // slots | edges << 32 of the frontier
+    unsigned long long *pk_out, *pk_clear;
+};
+
+// Inclusive prefix sum over the block of a 64-bit value; s_wave holds BLOCK/64.
+template <int BLOCK>
+__device__ __forceinline__ unsigned long long block_scan_incl64(unsigned long long v, unsigned long long *s_wave) {
 #pragma unroll
-    for (int u = 0; u < kScanItems; ++u) {
-        const int64_t p = base + threadIdx.x * kScanItems + u;
-        int32_t dg = 0;
-        if (p < nf) {
-            const int32_t v = q[p];
-            dg = ro[v + 1] - ro[v];
-        }
-        deg[u] = dg;
-        sum += dg;
+    for (int off = 1; off < kWave; off <<= 1) {
+        const unsigned long long o = __shfl_up(v, off, kWave);
+        if (lane_id() >= off) v += o;
     }
-    const int32_t incl = block_scan_incl<kScanThreads>(sum, s_wave);
-    int32_t run = incl - sum;
+    if (lane_id() == kWave - 1) s_wave[wave_id()] = v;
+    __syncthreads();
+    unsigned long long pre = 0;
 #pragma unroll
-    for (int u = 0; u < kScanItems; ++u) {
-        const int64_t p = base + threadIdx.x * kScanItems + u;
-        if (p < nf) offs[p] = run;
-        run += deg[u];
-    }
-    if (threadIdx.x == kScanThreads - 1) tile_sum[blockIdx.x] = incl;
-}
-
-// One block: exclusive prefix of the tile totals (in place), then
-// offs[nf] = E_f, meta = {E_f, T_f}.
-__global__ __launch_bounds__(1024) void frontier_scan_totals(const int32_t *__restrict__ cnt_in,
-                                                             int32_t *__restrict__ tile_sum,
-                                                             int32_t *__restrict__ offs,
-                                                             int32_t *__restrict__ meta) {
-    __shared__ int32_t s_wave[1024 / kWave];
-    __shared__ int32_t s_total;
-    const int32_t nf = *cnt_in;
-    const int32_t nb = (nf + kScanTile - 1) / kScanTile;
-    int32_t carry = 0;
-    for (int32_t c = 0; c < nb; c += 1024) {  // uniform across the block
-        const int32_t idx = c + static_cast<int32_t>(threadIdx.x);
-        const int32_t v = idx < nb ? tile_sum[idx] : 0;
-        const int32_t incl = block_scan_incl<1024>(v, s_wave);
-        if (idx < nb) tile_sum[idx] = carry + incl - v;
-        if (threadIdx.x == 1023) s_total = incl;
-        __syncthreads();
-        carry += s_total;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        offs[nf] = carry;
-        meta[0] = carry;
-        meta[1] = (nf + carry + kMergeW - 1) / kMergeW;
-    }
-}
-
-__global__ __launch_bounds__(256) void frontier_scan_add(const int32_t *__restrict__ cnt_in,
-                                                         const int32_t *__restrict__ tile_pre,
-                                                         int32_t *__restrict__ offs) {
-    const int32_t nf = *cnt_in;
-    for (int64_t p : grid_stride_range(0, nf)) offs[p] += tile_pre[p / kScanTile];
-}
-
-// Split at boundaries t in [0, T_f]: one group of kPartGroup lanes each.
-__global__ __launch_bounds__(256) void frontier_partition(const int32_t *__restrict__ cnt_in,
-                                                          const int32_t *__restrict__ offs,
-                                                          const int32_t *__restrict__ meta,
-                                                          int32_t *__restrict__ part_i,
-                                                          int32_t *__restrict__ part_j) {
-    const int32_t nf = *cnt_in, ef = meta[0], T = meta[1];
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * (256 / kPartGroup);
-    if (nf == 0 || first > T) return;  // uniform across the block
-    const int64_t t = first + threadIdx.x / kPartGroup;
-    const bool live = t <= T;  // uniform per group; every lane still takes part in the ballots
-    const int64_t total = static_cast<int64_t>(nf) + ef;
-    const int64_t tt = live ? t : T;
-    const int32_t d = static_cast<int32_t>(tt * kMergeW < total ? tt * kMergeW : total);
-    const int32_t i = group_merge_search<kPartGroup>(offs, nf, ef, d);
-    if (live && (threadIdx.x & (kPartGroup - 1)) == 0) {
-        part_i[t] = i;
-        part_j[t] = d - i;
-    }
+    for (int k = 0; k < BLOCK / kWave; ++k)
+        if (k < wave_id()) pre += s_wave[k];
+    __syncthreads();
+    return v + pre;
 }
 
 template <bool BFS>
-__global__ __launch_bounds__(kMergeBlock) void advance_merge_kernel(trav_args t, const int32_t *__restrict__ offs,
-                                                                    const int32_t *__restrict__ meta,
-                                                                    const int32_t *__restrict__ part_i,
-                                                                    const int32_t *__restrict__ part_j) {
-    // frontier entries touched by the unit: row ends relative to j0, the
-    // edge id of atom j of entry k is s_base[k] + j, and the entry's distance
-    __shared__ int32_t s_end[kMergeW + 1];
-    __shared__ int32_t s_base[kMergeW + 1];
-    __shared__ float s_du[BFS ? 1 : kMergeW + 1];
-    __shared__ int32_t s_wave[kMergeBlock / kWave];
-    __shared__ int32_t s_out;
-    const int32_t nf = frontier_size(t);
-    const int32_t T = nf > 0 ? meta[1] : 0;
+__global__ __launch_bounds__(kEdgeBlock) void advance_merge_kernel(trav_args t, edge_args x) {
+    __shared__ int32_t s_off[kEdgeSlots];   // first edge of the slot
+    __shared__ int32_t s_base[kEdgeSlots];  // edge e of the frontier, in this slot, is edge s_base + e of the graph
+    __shared__ float s_du[BFS ? 1 : kEdgeSlots];
+    __shared__ int32_t s_new[kEdgeNew];  // vertices for the next frontier
+    __shared__ unsigned long long s_wave[kEdgeBlock / kWave];
+    __shared__ unsigned long long s_got;
+    __shared__ int32_t s_iwave[kEdgeBlock / kWave];
+    __shared__ int32_t s_pair, s_held;
     const int tid = threadIdx.x;
-    for (int32_t u = blockIdx.x; u < T; u += gridDim.x) {  // uniform across the block
-        const int32_t i0 = part_i[u], j0 = part_j[u];
-        const int32_t i1 = part_i[u + 1], j1 = part_j[u + 1];
-        const int32_t nrows = i1 - i0, nnzs = j1 - j0;
-        const int32_t last = i1 < nf ? i1 : nf - 1;  // the entry holding the unit's trailing atoms
-        for (int32_t k = tid; k <= last - i0; k += kMergeBlock) {
-            const int32_t p = i0 + k;
-            const int32_t v = t.q_in[p];
-            s_end[k] = offs[p + 1] - j0;
-            s_base[k] = t.ro[v] - offs[p];
-            if constexpr (!BFS) s_du[k] = t.dist[v];
+    const bool live = *t.cnt_in != 0;
+    const unsigned long long pk = *x.pk_in;
+    if (blockIdx.x == 0 && tid == 0) {
+        *t.cnt_clear = 0;
+        *x.pk_clear = 0;
+        if (live) *t.rounds += 1;
+    }
+    const int32_t nf = static_cast<int32_t>(pk & 0xffffffffu), E = static_cast<int32_t>(pk >> 32);
+    const int32_t npairs = (nf + 1) / 2;
+    const int32_t units = (E + kEdgeUnit - 1) / kEdgeUnit;
+    // contiguous ranges of units: block b takes [b * units / grid, (b + 1) * units / grid)
+    const int32_t u0 = static_cast<int32_t>(static_cast<int64_t>(blockIdx.x) * units / gridDim.x);
+    const int32_t u1 = static_cast<int32_t>(static_cast<int64_t>(blockIdx.x + 1) * units / gridDim.x);
+    if (u0 >= u1) return;  // uniform
+    if (wave_id() == 0) {  // the last pair that starts at or before the range's first edge
+        const int32_t *off = x.off_in;
+        const int32_t c = group_count_below<kWave>(0, npairs, u0 * kEdgeUnit + 1, [off](int32_t q) { return off[q]; });
+        if (lane_id() == 0) s_pair = c - 1;
+    }
+    __syncthreads();
+    // Slots and edges for the n vertices held, a contiguous share per thread.
+    auto flush_new = [&](int32_t n) {  // every thread of the block
+        if (n == 0) return;
+        constexpr int S = kEdgeNew / kEdgeBlock;
+        const int32_t per = (n + kEdgeBlock - 1) / kEdgeBlock;
+        int32_t v[S], deg[S];
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+            const int32_t k = tid * per + i;
+            const bool in = i < per && k < n;
+            v[i] = in ? s_new[k] : 0;
+            deg[i] = in ? t.ro[v[i] + 1] - t.ro[v[i]] : 0;
+        }
+        unsigned long long mine = 0;
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+            if (deg[i] > 0) mine += (static_cast<unsigned long long>(deg[i]) << 32) | 1u;
+        const unsigned long long incl = block_scan_incl64<kEdgeBlock>(mine, s_wave);
+        if (tid == kEdgeBlock - 1) {
+            s_got = incl ? atomicAdd(x.pk_out, incl) : 0;
+            *t.cnt_out = 1;
         }
         __syncthreads();
-        // this thread's merge items [d, dend) of the unit's nrows + nnzs
-        const int32_t total = nrows + nnzs;
-        const int32_t d = tid * kMergeItems < total ? tid * kMergeItems : total;
-        const int32_t dend = d + kMergeItems < total ? d + kMergeItems : total;
-        int32_t lo = d - nnzs > 0 ? d - nnzs : 0;
-        int32_t hi = d < nrows ? d : nrows;
-        while (lo < hi) {
-            const int32_t mid = (lo + hi) >> 1;
-            if (s_end[mid] + mid < d)
-                lo = mid + 1;
-            else
-                hi = mid;
-        }
-        int32_t it = lo, jt = d - lo;
-        bool want[kMergeItems];
-        int32_t nv[kMergeItems];
-        int32_t mine = 0;
+        unsigned long long at = s_got + (incl - mine);
 #pragma unroll
-        for (int s = 0; s < kMergeItems; ++s) {
-            want[s] = false;
-            nv[s] = 0;
-            if (d + s < dend) {
-                if (it < nrows && s_end[it] <= jt) {
-                    ++it;  // entry it's edges are done
-                } else {
-                    const int32_t j = j0 + jt;
-                    want[s] = relax<BFS>(t, BFS ? 0.f : s_du[it], s_base[it] + j, nv[s]);
-                    ++jt;
+        for (int i = 0; i < S; ++i) {
+            if (deg[i] > 0) {
+                const uint32_t pos = static_cast<uint32_t>(at);
+                t.q_out[pos] = v[i];
+                if ((pos & 1) == 0) x.off_out[pos >> 1] = static_cast<int32_t>(at >> 32);
+                at += (static_cast<unsigned long long>(deg[i]) << 32) | 1u;
+            }
+        }
+        __syncthreads();
+    };
+    int32_t held = 0;
+    for (int32_t u = u0; u < u1; ++u) {  // uniform across the block
+        const int32_t e0 = u * kEdgeUnit;
+        const int32_t e1 = E - e0 < kEdgeUnit ? E : e0 + kEdgeUnit;
+        const int32_t p0 = s_pair;
+        int32_t slots = 0;  // staged, of pairs that begin in the unit or before it
+        for (int32_t b = 0;; b += kEdgeBlock) {  // uniform
+            const int32_t q = p0 + b + tid, at = 2 * (b + tid);
+            int32_t o0 = INT32_MAX, o1 = INT32_MAX;
+            if (q < npairs) {
+                o0 = x.off_in[q];
+                if (o0 < e1) {
+                    const bool two = 2 * q + 1 < nf;
+                    const int32_t v0 = t.q_in[2 * q], v1 = t.q_in[two ? 2 * q + 1 : 2 * q];
+                    const int32_t f0 = t.ro[v0], l0 = t.ro[v0 + 1], f1 = t.ro[v1];
+                    if (two) o1 = o0 + (l0 - f0);
+                    s_base[at] = f0 - o0;
+                    s_base[at + 1] = f1 - o1;
+                    if constexpr (!BFS) {
+                        s_du[at] = t.dist[v0];
+                        s_du[at + 1] = t.dist[v1];
+                    }
                 }
             }
-            mine += want[s] ? 1 : 0;
+            s_off[at] = o0;
+            s_off[at + 1] = o1;
+            const int32_t pairs = __syncthreads_count(o0 < e1);
+            slots += 2 * pairs;
+            if (pairs < kEdgeBlock) break;
         }
-        // the unit's new frontier vertices go out with one atomic per block:
-        // a block prefix sum of the threads' counts places each thread's run
-        const int32_t incl = block_scan_incl<kMergeBlock>(mine, s_wave);
-        if (tid == kMergeBlock - 1) s_out = incl > 0 ? atomicAdd(t.cnt_out, incl) : 0;
-        __syncthreads();
-        int32_t pos = s_out + incl - mine;
+        // each edge's slot: the last with s_off <= e
+        int32_t slot[kEdgeItems];
 #pragma unroll
-        for (int s = 0; s < kMergeItems; ++s)
-            if (want[s]) t.q_out[pos++] = nv[s];
+        for (int i = 0; i < kEdgeItems; ++i) slot[i] = 0;
+        int32_t step = 1;
+        while (step < slots) step <<= 1;
+        for (step >>= 1; step > 0; step >>= 1) {  // uniform
+#pragma unroll
+            for (int i = 0; i < kEdgeItems; ++i) {
+                const int32_t at = slot[i] + step;
+                if (at < slots && s_off[at < slots ? at : 0] <= e0 + tid + i * kEdgeBlock) slot[i] = at;
+            }
+        }
+        int32_t v[kEdgeItems];
+        float offer[kEdgeItems];
+        bool want[kEdgeItems];
+#pragma unroll
+        for (int i = 0; i < kEdgeItems; ++i) {
+            const int32_t e = e0 + tid + i * kEdgeBlock;
+            want[i] = e < e1;
+            v[i] = 0;
+            offer[i] = 0.f;
+            if (want[i]) {
+                const int32_t g = s_base[slot[i]] + e;
+                v[i] = ld_stream(t.ci + g);
+                if constexpr (!BFS) offer[i] = ld_stream(t.w + g);
+            }
+            if (e == e1 - 1) s_pair = p0 + slot[i] / 2;  // the next unit begins in this pair or after it
+        }
+        // the target's state, which only falls (SSSP) or is claimed once (BFS): a
+        // stale read lets an offer through to the atomic, which decides
+        if constexpr (BFS) {
+            int32_t seen[kEdgeItems];
+#pragma unroll
+            for (int i = 0; i < kEdgeItems; ++i) seen[i] = want[i] ? t.depth[v[i]] : 0;
+#pragma unroll
+            for (int i = 0; i < kEdgeItems; ++i)
+                if (want[i] && seen[i] == kUnvisited) seen[i] = atomicCAS(t.depth + v[i], kUnvisited, t.iter + 1);
+#pragma unroll
+            for (int i = 0; i < kEdgeItems; ++i) want[i] = want[i] && seen[i] == kUnvisited;
+        } else {
+            float seen[kEdgeItems];
+#pragma unroll
+            for (int i = 0; i < kEdgeItems; ++i) {
+                offer[i] = s_du[slot[i]] + offer[i];
+                seen[i] = want[i] ? t.dist[v[i]] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < kEdgeItems; ++i) {
+                want[i] = want[i] && offer[i] < seen[i];
+                if (want[i])
+                    seen[i] = __int_as_float(
+                        atomicMin(reinterpret_cast<int32_t *>(t.dist) + v[i], __float_as_int(offer[i])));
+            }
+            int32_t last[kEdgeItems];
+#pragma unroll
+            for (int i = 0; i < kEdgeItems; ++i) {
+                want[i] = want[i] && offer[i] < seen[i];
+                last[i] = want[i] ? atomicExch(t.stamp + v[i], t.iter) : 0;
+            }
+#pragma unroll
+            for (int i = 0; i < kEdgeItems; ++i) want[i] = want[i] && last[i] != t.iter;
+        }
+        // the unit's new vertices join the block's
+        int32_t mine = 0;
+#pragma unroll
+        for (int i = 0; i < kEdgeItems; ++i) mine += want[i] ? 1 : 0;
+        const int32_t incl = block_scan_incl<kEdgeBlock>(mine, s_iwave);
+        int32_t at = held + incl - mine;
+#pragma unroll
+        for (int i = 0; i < kEdgeItems; ++i)
+            if (want[i]) s_new[at++] = v[i];
+        if (tid == kEdgeBlock - 1) s_held = held + incl;
         __syncthreads();
+        held = s_held;  // (the next unit's scan orders this read before the next write)
+        if (held > kEdgeNew - kEdgeUnit || u + 1 == u1) {  // uniform
+            flush_new(held);
+            held = 0;
+        }
     }
 }
 
 template <bool BFS>
 __global__ __launch_bounds__(256) void traversal_init_kernel(int32_t n, int32_t source, float *dist,
                                                              int32_t *depth, int32_t *stamp, int32_t *q0,
-                                                             int32_t *counters) {
+                                                             int32_t *counters, const int32_t *ro, int32_t *off0,
+                                                             unsigned long long *pk) {
     for (int64_t v : grid_stride_range(0, n)) {
         if constexpr (BFS) {
             depth[v] = v == source ? 0 : kUnvisited;
@@ -431,6 +481,11 @@ __global__ __launch_bounds__(256) void traversal_init_kernel(int32_t n, int32_t 
         counters[3] = 0;  // rounds
         counters[4] = 0;  // work-queue tickets of the first two launches
         counters[5] = 0;
+        // merge-path: the source's slot and edges
+        const int32_t d = ro[source + 1] - ro[source];
+        off0[0] = 0;
+        pk[0] = d > 0 ? (static_cast<unsigned long long>(d) << 32) | 1u : 0u;
+        pk[1] = pk[2] = 0;
     }
 }
 
@@ -452,29 +507,17 @@ hipError_t launch_advance(K kernel, int block, int grid, const trav_args &t, hip
 }
 
 template <bool BFS>
-hipError_t advance_merge(const csr_dev &G, const trav_cfg &c, const trav_ws &w, const trav_args &t, hipStream_t s) {
-    const int64_t n = G.rows;
-    const int64_t scan_blocks = (n + kScanTile - 1) / kScanTile;
-    hipLaunchKernelGGL(frontier_scan_tiles, dim3(static_cast<uint32_t>(scan_blocks)), dim3(kScanThreads), 0, s,
-                       t.q_in, t.cnt_in, G.ro, w.offs, w.tile_sum);
-    hipLaunchKernelGGL(frontier_scan_totals, dim3(1), dim3(1024), 0, s, t.cnt_in, w.tile_sum, w.offs, w.meta);
-    const int64_t add_blocks = (n + 255) / 256 < 2048 ? (n + 255) / 256 : 2048;
-    hipLaunchKernelGGL(frontier_scan_add, dim3(static_cast<uint32_t>(add_blocks)), dim3(256), 0, s, t.cnt_in,
-                       w.tile_sum, w.offs);
-    const int64_t tmax = trav_merge_units(n, G.nnz);
-    const int64_t part_blocks = ((tmax + 1) * kPartGroup + 255) / 256;
-    hipLaunchKernelGGL(frontier_partition, dim3(static_cast<uint32_t>(part_blocks)), dim3(256), 0, s, t.cnt_in,
-                       w.offs, w.meta, w.part_i, w.part_j);
-    const int grid = c.grid > 0 ? c.grid : resident_blocks(advance_merge_kernel<BFS>, kMergeBlock);
-    hipLaunchKernelGGL(advance_merge_kernel<BFS>, dim3(static_cast<uint32_t>(grid)), dim3(kMergeBlock), 0, s, t,
-                       w.offs, w.meta, w.part_i, w.part_j);
+hipError_t advance_merge(const trav_cfg &c, const trav_ws &w, const trav_args &t, hipStream_t s) {
+    const int32_t i = t.iter;
+    const edge_args x{w.off[i & 1], w.off[(i + 1) & 1], w.pk + i % 3, w.pk + (i + 1) % 3, w.pk + (i + 2) % 3};
+    hipLaunchKernelGGL(advance_merge_kernel<BFS>, dim3(static_cast<uint32_t>(c.grid)), dim3(kEdgeBlock), 0, s, t, x);
     return hipGetLastError();
 }
 
 template <bool BFS>
-hipError_t advance(const csr_dev &G, const trav_cfg &c, const trav_ws &w, const trav_args &t, hipStream_t s) {
+hipError_t advance(const trav_cfg &c, const trav_ws &w, const trav_args &t, hipStream_t s) {
     prof_scope p(s, BFS ? "bfs_advance" : "sssp_advance");
-    if (c.kind == LB_MERGE_PATH) return advance_merge<BFS>(G, c, w, t, s);
+    if (c.kind == LB_MERGE_PATH) return advance_merge<BFS>(c, w, t, s);
     if (c.kind == LB_THREAD_MAPPED) return launch_advance(advance_thread_kernel<BFS>, c.block, c.grid, t, s);
 #define LB_G(G)                                                                                               \
     if (c.group == G) {                                                                                       \
@@ -490,23 +533,28 @@ hipError_t advance(const csr_dev &G, const trav_cfg &c, const trav_ws &w, const 
 }
 
 template <bool BFS>
-hipError_t run_traversal(const csr_dev &G, int32_t source, float *dist, int32_t *depth, const trav_cfg &c,
+hipError_t run_traversal(const csr_dev &G, int32_t source, float *dist, int32_t *depth, trav_cfg c,
                          int32_t max_iter, int32_t *iterations, bool *converged, void *ws, hipStream_t s) {
-    const trav_ws w = trav_ws_carve(ws, G.rows, G.nnz);
+    const trav_ws w = trav_ws_carve(ws, G.rows);
     {
         prof_scope p(s, "traversal_init");
         const int64_t blocks = (static_cast<int64_t>(G.rows) + 255) / 256;
         hipLaunchKernelGGL(traversal_init_kernel<BFS>, dim3(static_cast<uint32_t>(blocks < 8192 ? blocks : 8192)),
-                           dim3(256), 0, s, G.rows, source, dist, depth, w.stamp, w.queue[0], w.counters);
+                           dim3(256), 0, s, G.rows, source, dist, depth, w.stamp, w.queue[0], w.counters, G.ro, w.off[0], w.pk);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     trav_args t{G.ro, G.ci, static_cast<const float *>(G.val), dist, depth, w.stamp,
                 nullptr, nullptr, nullptr, nullptr, nullptr, w.counters + 3, nullptr, nullptr, 0};
-    int32_t launched = 0, batch = 4;
+    // Batches of 4 iterations up to 16, then doubling to 32: a power-law graph ends
+    // within 16, and what is launched past the end is wasted (batches of 4, 8 and 16
+    // launched 28 iterations for 13); a long chain or grid pays for each wait.
+    int32_t launched = 0;
+    if (c.kind == LB_MERGE_PATH && c.grid <= 0) c.grid = resident_blocks(advance_merge_kernel<BFS>, kEdgeBlock);
     int32_t host[4] = {0, 0, 0, 0};
     *converged = false;
     for (;;) {
+        const int32_t batch = launched < 16 ? 4 : (launched < 32 ? launched : 32);
         for (int k = 0; k < batch && launched < max_iter; ++k, ++launched) {
             t.iter = launched;
             t.q_in = w.queue[launched & 1];
@@ -516,7 +564,7 @@ hipError_t run_traversal(const csr_dev &G, int32_t source, float *dist, int32_t 
             t.cnt_clear = w.counters + (launched + 2) % 3;
             t.ticket = w.counters + 4 + (launched & 1);
             t.ticket_clear = w.counters + 4 + ((launched + 1) & 1);
-            const hipError_t e = advance<BFS>(G, c, w, t, s);
+            const hipError_t e = advance<BFS>(c, w, t, s);
             if (e != hipSuccess) return e;
         }
         hipError_t e = hipMemcpyAsync(host, w.counters, sizeof host, hipMemcpyDeviceToHost, s);
@@ -527,7 +575,6 @@ hipError_t run_traversal(const csr_dev &G, int32_t source, float *dist, int32_t 
             break;
         }
         if (launched >= max_iter) break;
-        batch = batch * 2 < 32 ? batch * 2 : 32;
     }
     if (iterations) *iterations = host[3];
     return hipSuccess;

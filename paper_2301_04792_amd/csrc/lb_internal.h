@@ -341,49 +341,36 @@ struct trav_cfg {
     int grid;              // 0 = resident grid
 };
 
-// Merge-path units of a frontier: at most (n + nnz) merge items of 2048.
-inline int64_t trav_merge_units(int64_t n, int64_t nnz) { return (n + nnz + 2047) / 2048; }
-
 // Workspace: stamp[n], two frontier queues of n vertex ids, counters (three
 // rotating frontier sizes, the count of non-empty frontiers, two rotating
-// work-queue tickets);
-// for merge-path also the frontier's offsets[n + 1], per-tile degree sums,
-// {E_f, T_f} and the split at every unit boundary.
+// work-queue tickets; at byte 64, three rotating 64-bit {slots, edges} of the
+// merge-path frontier), and the merge-path frontiers' offsets of even slots
+// (2 ceil(n / 2) <= n + 1).  The size also covers a split at every 2048 merge
+// items, which nothing uses any more: callers may keep workspaces by size.
 struct trav_ws {
     int32_t *stamp;
     int32_t *queue[2];
     int32_t *counters;
-    int32_t *offs;
-    int32_t *tile_sum;
-    int32_t *meta;
-    int32_t *part_i;
-    int32_t *part_j;
+    int32_t *off[2];
+    unsigned long long *pk;
 };
 inline size_t trav_ws_bytes(int64_t n, int64_t nnz) {
     const size_t q = align256(static_cast<size_t>(n) * 4);
-    const size_t units = static_cast<size_t>(trav_merge_units(n, nnz)) + 1;
+    const size_t units = static_cast<size_t>((n + nnz + 2047) / 2048) + 1;
     return 3 * q + 256 + align256(static_cast<size_t>(n + 1) * 4) + align256(static_cast<size_t>(n / 2048 + 2) * 4) +
            256 + 2 * align256(units * 4);
 }
-inline trav_ws trav_ws_carve(void *base, int64_t n, int64_t nnz) {
+inline trav_ws trav_ws_carve(void *base, int64_t n) {
     char *p = static_cast<char *>(base);
     const size_t q = align256(static_cast<size_t>(n) * 4);
-    const size_t units = static_cast<size_t>(trav_merge_units(n, nnz)) + 1;
     trav_ws w;
     w.stamp = reinterpret_cast<int32_t *>(p);
     w.queue[0] = reinterpret_cast<int32_t *>(p + q);
     w.queue[1] = reinterpret_cast<int32_t *>(p + 2 * q);
     w.counters = reinterpret_cast<int32_t *>(p + 3 * q);
-    p += 3 * q + 256;
-    w.offs = reinterpret_cast<int32_t *>(p);
-    p += align256(static_cast<size_t>(n + 1) * 4);
-    w.tile_sum = reinterpret_cast<int32_t *>(p);
-    p += align256(static_cast<size_t>(n / 2048 + 2) * 4);
-    w.meta = reinterpret_cast<int32_t *>(p);
-    p += 256;
-    w.part_i = reinterpret_cast<int32_t *>(p);
-    p += align256(units * 4);
-    w.part_j = reinterpret_cast<int32_t *>(p);
+    w.pk = reinterpret_cast<unsigned long long *>(p + 3 * q + 64);
+    w.off[0] = reinterpret_cast<int32_t *>(p + 3 * q + 256);
+    w.off[1] = w.off[0] + (n + 1) / 2;
     return w;
 }
 bool traversal_group_supported(int g);
