@@ -42,7 +42,8 @@ __global__ __launch_bounds__(256) void coo_partition_kernel(const int32_t *__res
     }
 }
 
-template <int BLOCK, int ITEMS, typename VT>
+// SHORT: units of short rows only are summed a row per thread.
+template <int BLOCK, int ITEMS, typename VT, bool SHORT>
 __global__ __launch_bounds__(BLOCK) void coo_spmv_consume(
     int32_t rows, int32_t nnz, const int32_t *__restrict__ ri, const int32_t *__restrict__ ci,
     const VT *__restrict__ val, const VT *__restrict__ x, float *__restrict__ y, const int32_t *__restrict__ part_i,
@@ -100,7 +101,14 @@ __global__ __launch_bounds__(BLOCK) void coo_spmv_consume(
     }
     __syncthreads();
 
-    // From here on, the CSR consume: thread diagonal, walk, segmented scan.
+    // From here on, the CSR consume: short rows by a thread each, else thread
+    // diagonal, walk, segmented scan.
+    if constexpr (SHORT) {
+        if (sum_short_rows<BLOCK>(s_re, s_pv, nrows, nnzs, y + i0, carry_val + b)) {
+            if (tid == 0) carry_row[b] = i1;
+            return;
+        }
+    }
     const int32_t total = nrows + nnzs;
     const int32_t d = tid * ITEMS < total ? tid * ITEMS : total;
     const int32_t dend = d + ITEMS < total ? d + ITEMS : total;
@@ -182,8 +190,9 @@ hipError_t run_coo_merge(const coo_dev &A, const void *x, float *y, void *ws, hi
     if (e != hipSuccess) return e;
     {
         prof_scope p(s, "coo_consume");
-        hipLaunchKernelGGL((coo_spmv_consume<BLOCK, ITEMS, VT>), dim3(static_cast<uint32_t>(T)), dim3(BLOCK), 0, s,
-                           A.rows, A.nnz, A.ri, A.ci, static_cast<const VT *>(A.val), static_cast<const VT *>(x), y,
+        auto kern = short_rows_on_average(A.rows, A.nnz) ? coo_spmv_consume<BLOCK, ITEMS, VT, true>
+                                                         : coo_spmv_consume<BLOCK, ITEMS, VT, false>;
+        hipLaunchKernelGGL(kern, dim3(static_cast<uint32_t>(T)), dim3(BLOCK), 0, s, A.rows, A.nnz, A.ri, A.ci, static_cast<const VT *>(A.val), static_cast<const VT *>(x), y,
                            w.part_i, w.part_j, w.carry_row, w.carry_val);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -121,8 +121,12 @@ hipError_t merge_partition(const int32_t *ro, int32_t rows, int32_t nnz, int32_t
 // the bytes in flight per instruction.  The x gathers of a wavefront then
 // stride by 4 nonzeros, which costs the line sharing that lane-consecutive
 // gathers get from long sorted rows, so this form pays only where columns
-// are local (a stencil).  The launcher requires nnz >= 4 and aligned
-// col_idx / values.
+// are local (a stencil) or rows too short to share lines.  The launcher
+// requires nnz >= 4 and aligned col_idx / values.
+// VEC = 2 (unplanned, a matrix of at most kShortMean nonzeros a row on average):
+// four per lane and load in units whose rows average that little, one in the
+// others.  VEC = 0: the same matrix, unaligned or through vperm: one per lane.
+// VEC 0, 2 and 4, unplanned: a unit of short rows only is summed a row per thread.
 // PLAN (planned SpMV, short rows only): block b takes the b-th active unit
 // (T is then the number of active units) and reads its record from the
 // plan (the split, the product range, the head, the long flag); each
@@ -147,7 +151,9 @@ __global__ __launch_bounds__(BLOCK) void merge_spmv_consume(
     const plan_unit *__restrict__ units = nullptr) {
     static_assert(BANDS == 1 || BANDS == 2, "one or two column bands");
     static_assert(!(VPERM && BANDS != 1), "permuted values with one band only");
-    static_assert(VEC == 1 || (VEC == 4 && BANDS == 1 && !VPERM && ITEMS % 4 == 0), "vector loads: one band");
+    static_assert(VEC == 0 || VEC == 1 || ((VEC == 4 || VEC == 2) && BANDS == 1 && !VPERM && ITEMS % 4 == 0),
+                  "vector loads: one band");
+    static_assert(VEC != 0 || (BANDS == 1 && !PLAN), "short rows: one band, unplanned");
     static_assert(!PLAN || !VPERM, "planned form: own values");
     constexpr int W = BLOCK * ITEMS;
     __shared__ int32_t s_buf[W];  // row ends [0, nrows), then products [nrows, nrows + nnzs)
@@ -216,8 +222,6 @@ __global__ __launch_bounds__(BLOCK) void merge_spmv_consume(
     // nonzero loads are clamped into [nz_first, nz_last], valid indices
     const int32_t nz_last = jb > ja ? jb - 1 : (ja < nnz ? ja : nnz - 1);
     const int32_t nz_first = ja < nz_last ? ja : nz_last;
-    int32_t re[ITEMS], c[ITEMS];
-    float pv[ITEMS];
     // planned: each thread's first nonzero of row i0's head goes out before
     // the stream loads, its x gather right after them
     const bool has_head = PLAN && h0 + tid < j0;
@@ -231,7 +235,11 @@ __global__ __launch_bounds__(BLOCK) void merge_spmv_consume(
     auto head_gather = [&]() {
         if (has_head && (BANDS == 1 || (hc >= cb) == (band == 1))) hx = to_f32(x[hc]);
     };
-    if constexpr (VEC == 4) {
+    // four nonzeros per lane and load (VEC = 2: in units of short rows)
+    const bool four = VEC == 4 || (VEC == 2 && nnzs <= kShortMean * nrows);  // uniform
+    if (four) {
+        int32_t re[ITEMS], c[ITEMS];
+        float pv[ITEMS];
         using vec_t = typename vec4_of<VT>::type;
         typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
         // groups [vs, vs + 4) with vs a multiple of 4: the block's W / 4
@@ -275,66 +283,68 @@ __global__ __launch_bounds__(BLOCK) void merge_spmv_consume(
         const int32_t g = (cov_end > j0 ? cov_end : j0) + tid;
         if (tid < 3 && g < j1)
             s_pv[g - j0] = PLAN && (g < ja || g >= jb) ? 0.f : to_f32(val[g]) * to_f32(x[ci[g]]);
-    } else if constexpr (BANDS == 1) {
-        VT v[ITEMS];
-        float xv[ITEMS];
-        int32_t vp[VPERM ? ITEMS : 1];
+    } else if constexpr (VEC != 4) {
+        int32_t re[ITEMS], c[ITEMS];
+        float pv[ITEMS];
+        if constexpr (BANDS == 1) {
+            VT v[ITEMS];
+            float xv[ITEMS];
+            int32_t vp[VPERM ? ITEMS : 1];
 #pragma unroll
-        for (int u = 0; u < ITEMS; ++u) {
-            const int32_t k = tid + u * BLOCK;
-            const int32_t rk = i0 + 1 + k;
-            const int32_t jk = j0 + k;
-            const int32_t jc = jk < nz_first ? nz_first : (jk < nz_last ? jk : nz_last);
-            re[u] = ro[rk < re_last ? rk : re_last];
-            if constexpr (VPERM != 2) c[u] = ld_stream(ci + jc);
-            if constexpr (VPERM)
-                vp[u] = ld_stream(vperm + jc);
-            else
-                v[u] = ld_stream(val + jc);
-        }
-        head_gather();
+            for (int u = 0; u < ITEMS; ++u) {
+                const int32_t k = tid + u * BLOCK;
+                const int32_t rk = i0 + 1 + k;
+                const int32_t jk = j0 + k;
+                const int32_t jc = jk < nz_first ? nz_first : (jk < nz_last ? jk : nz_last);
+                re[u] = ro[rk < re_last ? rk : re_last];
+                if constexpr (VPERM != 2) c[u] = ld_stream(ci + jc);
+                if constexpr (VPERM)
+                    vp[u] = ld_stream(vperm + jc);
+                else
+                    v[u] = ld_stream(val + jc);
+            }
+            head_gather();
 #pragma unroll
-        for (int u = 0; u < ITEMS; ++u) {
-            if constexpr (VPERM) v[u] = val[vp[u]];
-            if constexpr (VPERM != 2) xv[u] = to_f32(x[c[u]]);
-        }
+            for (int u = 0; u < ITEMS; ++u) {
+                if constexpr (VPERM) v[u] = val[vp[u]];
+                if constexpr (VPERM != 2) xv[u] = to_f32(x[c[u]]);
+            }
 #pragma unroll
-        for (int u = 0; u < ITEMS; ++u) {
-            if constexpr (VPERM == 2)
-                pv[u] = v[u];
-            else
-                pv[u] = to_f32(v[u]) * xv[u];
-            if constexpr (PLAN) {
-                const int32_t jk = j0 + tid + u * BLOCK;
-                if (jk < ja || jk >= jb) pv[u] = 0.f;
+            for (int u = 0; u < ITEMS; ++u) {
+                if constexpr (VPERM == 2)
+                    pv[u] = v[u];
+                else
+                    pv[u] = to_f32(v[u]) * xv[u];
+                if constexpr (PLAN) {
+                    const int32_t jk = j0 + tid + u * BLOCK;
+                    if (jk < ja || jk >= jb) pv[u] = 0.f;
+                }
+            }
+        } else {
+            // band 0 takes col < cb, band 1 col >= cb: x is gathered only for a
+            // nonzero of the block's own band
+            VT v[ITEMS];
+#pragma unroll
+            for (int u = 0; u < ITEMS; ++u) {
+                const int32_t k = tid + u * BLOCK;
+                const int32_t rk = i0 + 1 + k;
+                const int32_t jk = j0 + k;
+                const int32_t jc = jk < nz_first ? nz_first : (jk < nz_last ? jk : nz_last);
+                re[u] = ro[rk < re_last ? rk : re_last];
+                c[u] = ci[jc];
+                v[u] = val[jc];
+            }
+            head_gather();
+#pragma unroll
+            for (int u = 0; u < ITEMS; ++u) {
+                bool mine = (c[u] >= cb) == (band == 1);
+                if constexpr (PLAN) {
+                    const int32_t jk = j0 + tid + u * BLOCK;
+                    mine = mine && jk >= ja && jk < jb;
+                }
+                pv[u] = mine ? to_f32(v[u]) * to_f32(x[c[u]]) : 0.f;
             }
         }
-    } else {
-        // band 0 takes col < cb, band 1 col >= cb: x is gathered only for a
-        // nonzero of the block's own band
-        VT v[ITEMS];
-#pragma unroll
-        for (int u = 0; u < ITEMS; ++u) {
-            const int32_t k = tid + u * BLOCK;
-            const int32_t rk = i0 + 1 + k;
-            const int32_t jk = j0 + k;
-            const int32_t jc = jk < nz_first ? nz_first : (jk < nz_last ? jk : nz_last);
-            re[u] = ro[rk < re_last ? rk : re_last];
-            c[u] = ci[jc];
-            v[u] = val[jc];
-        }
-        head_gather();
-#pragma unroll
-        for (int u = 0; u < ITEMS; ++u) {
-            bool mine = (c[u] >= cb) == (band == 1);
-            if constexpr (PLAN) {
-                const int32_t jk = j0 + tid + u * BLOCK;
-                mine = mine && jk >= ja && jk < jb;
-            }
-            pv[u] = mine ? to_f32(v[u]) * to_f32(x[c[u]]) : 0.f;
-        }
-    }
-    if constexpr (VEC == 1) {
 #pragma unroll
         for (int u = 0; u < ITEMS; ++u) {
             const int k = tid + u * BLOCK;
@@ -381,6 +391,15 @@ __global__ __launch_bounds__(BLOCK) void merge_spmv_consume(
                 for (int32_t j = lo; j < hi; ++j) acc += s_pv[j];
                 if (!(k == 0 && skip_first)) y[i0 + k] = acc;
             }
+            return;
+        }
+    }
+
+    // Unplanned, one band: the same for a unit that turns out to have short rows
+    // only; its first row's earlier part comes with the carries.
+    if constexpr (!PLAN && BANDS == 1 && VEC != 1) {
+        if (sum_short_rows<BLOCK>(s_re, s_pv, nrows, nnzs, y + i0, carry_val + b)) {
+            if (tid == 0) carry_row[b] = i1;
             return;
         }
     }
@@ -570,11 +589,20 @@ static hipError_t run_merge_spmv(const csr_dev &A, const void *x, float *y, int 
         const VT *val = static_cast<const VT *>(A.val);
         const int32_t cb = static_cast<int32_t>((A.cols + 1) / 2);
         const dim3 xcd_grid(static_cast<uint32_t>((T + kXcds - 1) / kXcds * kXcds));
-        if (prod) {
+        const bool short_rows = short_rows_on_average(A.rows, A.nnz);
+        if (prod && short_rows) {
+            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, float, float, 1, 2, 0>), xcd_grid, dim3(BLOCK), 0, s,
+                               A.rows, A.nnz, A.ro, A.ci, prod, nullptr, y, w.part_i, w.part_j, w.carry_row,
+                               w.carry_val, static_cast<int32_t>(T), cb, y_hi, vperm);
+        } else if (prod) {
             hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, float, float, 1, 2>), xcd_grid, dim3(BLOCK), 0, s,
                                A.rows, A.nnz, A.ro, A.ci, prod, nullptr, y, w.part_i, w.part_j, w.carry_row,
                                w.carry_val, static_cast<int32_t>(T), cb, y_hi, vperm);
-        } else if (vperm) {  // x is float32 (the backward's dy) whatever the value type
+        } else if (vperm && short_rows) {  // x is float32 (the backward's dy) whatever the value type
+            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, float, 1, 1, 0>), xcd_grid, dim3(BLOCK), 0, s,
+                               A.rows, A.nnz, A.ro, A.ci, val, static_cast<const float *>(x), y, w.part_i, w.part_j,
+                               w.carry_row, w.carry_val, static_cast<int32_t>(T), cb, y_hi, vperm);
+        } else if (vperm) {
             hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, float, 1, 1>), xcd_grid, dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, val, static_cast<const float *>(x), y,
                                w.part_i, w.part_j, w.carry_row, w.carry_val, static_cast<int32_t>(T), cb, y_hi, vperm);
         } else if (vec == 4 && vector_loads_ok(A)) {
@@ -586,6 +614,16 @@ static hipError_t run_merge_spmv(const csr_dev &A, const void *x, float *y, int 
             const int64_t per = kXcds / 2;  // units per row of kXcds blocks
             const int64_t grid = (T + per - 1) / per * kXcds;
             hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 2>), dim3(static_cast<uint32_t>(grid)),
+                               dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, val, static_cast<const VT *>(x), y,
+                               w.part_i, w.part_j, w.carry_row, w.carry_val, static_cast<int32_t>(T), cb, y_hi,
+                               nullptr);
+        } else if (short_rows && !vector_loads_ok(A)) {
+            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 1, 0, 0>), dim3(static_cast<uint32_t>(T)),
+                               dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, val, static_cast<const VT *>(x), y,
+                               w.part_i, w.part_j, w.carry_row, w.carry_val, static_cast<int32_t>(T), cb, y_hi,
+                               nullptr);
+        } else if (short_rows) {
+            hipLaunchKernelGGL((merge_spmv_consume<BLOCK, ITEMS, VT, VT, 1, 0, 2>), dim3(static_cast<uint32_t>(T)),
                                dim3(BLOCK), 0, s, A.rows, A.nnz, A.ro, A.ci, val, static_cast<const VT *>(x), y,
                                w.part_i, w.part_j, w.carry_row, w.carry_val, static_cast<int32_t>(T), cb, y_hi,
                                nullptr);

@@ -262,6 +262,35 @@ __device__ __forceinline__ seg_t block_seg_scan_excl(seg_t x, seg_t *s_wave, seg
     return lane ? seg_combine(pre, seg_t{pv, pf}) : pre;
 }
 
+// A merge-path unit staged in LDS (row ends s_re[0, nrows) relative to the
+// unit, products s_pv[0, nnzs)) whose rows, and the open row at its end, each hold
+// at most kShortRow of its nonzeros: a thread sums whole rows left to right,
+// writes y0[k] for the row k that closes and the open row's sum to *open, with no
+// diagonal search, walk or scan.  Returns false, having done nothing, for any
+// other unit (uniform; every thread of the block calls it after a barrier).
+constexpr int kShortRow = 16;
+template <int BLOCK>
+__device__ __forceinline__ bool sum_short_rows(const int32_t *s_re, const float *s_pv, int32_t nrows, int32_t nnzs,
+                                               float *__restrict__ y0, float *__restrict__ open) {
+    if (nnzs > kShortRow * (nrows + 1)) return false;  // uniform
+    bool is_long = false;
+    for (int32_t k = threadIdx.x; k <= nrows; k += BLOCK) {
+        const int32_t lo = k ? s_re[k - 1] : 0, hi = k < nrows ? s_re[k] : nnzs;
+        is_long = is_long || hi - lo > kShortRow;
+    }
+    if (__syncthreads_or(is_long)) return false;
+    for (int32_t k = threadIdx.x; k <= nrows; k += BLOCK) {
+        const int32_t lo = k ? s_re[k - 1] : 0, hi = k < nrows ? s_re[k] : nnzs;
+        float acc = 0.f;
+        for (int32_t j = lo; j < hi; ++j) acc += s_pv[j];
+        if (k < nrows)
+            y0[k] = acc;
+        else
+            *open = acc;
+    }
+    return true;
+}
+
 // Block-wide sum (all threads call; every thread gets the total).  s_red
 // holds BLOCK/64 floats.  Waves are added in index order: deterministic.
 template <int BLOCK>
