@@ -89,46 +89,50 @@ __global__ __launch_bounds__(256) void gemm_products_rows(gemm_args g, int64_t *
     }
 }
 
-// For short rows: group_mapped_scan over A's rows: a wavefront takes 64 rows and strides
-// their flattened entries, so short and long rows share the lanes; each
-// step sums its entries' B row lengths per row (a segmented sum over the
-// lanes) into the rows' LDS counters (exact, int64).
+// For short rows: a block takes kProdRows rows and strides their entries, which
+// are one range of A's; an entry's row is found among the row ends in LDS and its
+// B row's length added to the row's LDS counter (exact, int64).    (Rows dealt
+// to wavefronts 64 at a time, a segmented scan per step, took 30 us for 1M rows
+// of five.)
+constexpr int kProdRows = 512;
 __global__ __launch_bounds__(256) void gemm_products(gemm_args g, int64_t *__restrict__ prod) {
-    using sched = group_mapped_scan<kWave, csr_tile_set>;
-    __shared__ typename sched::storage s_st[sched::GPB];
-    __shared__ unsigned long long s_cnt[sched::GPB][kWave];
-    const int gi = threadIdx.x / kWave, gl = lane_id();
-    sched sch(csr_tile_set{g.a_ro, g.m, 0}, s_st);
-    for (int64_t round : sch.rounds()) {  // uniform across the block
-        s_cnt[gi][gl] = 0;
-        const int32_t total = sch.load(round);  // ends with a barrier: the counters are clear
-        const int32_t steps = (total + kWave - 1) / kWave;
-        for (int32_t st = 0; st < steps; ++st) {  // uniform within the wavefront
-            const int32_t at = st * kWave + gl;
-            int32_t q = kWave;  // past the last row: inactive lane
-            unsigned long long v = 0;
-            if (at < total) {
-                q = sch.get_tile(at);
-                const int32_t j = g.a_ci[sch.atom(at, q)];
-                v = static_cast<unsigned long long>(g.b_ro[j + 1] - g.b_ro[j]);
-            }
-            // the step's atoms are in row order: sum each run of equal q over
-            // the lanes, then its last lane adds the run to the row's counter
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-                const unsigned long long v2 = __shfl_up(v, off, kWave);
-                const int32_t q2 = __shfl_up(q, off, kWave);
-                if (gl >= off && q2 == q) v += v2;
-            }
-            const int32_t qn = __shfl_down(q, 1, kWave);
-            if (q < kWave && (gl == kWave - 1 || qn != q)) s_cnt[gi][q] += v;
-            __builtin_amdgcn_wave_barrier();
-        }
-        __syncthreads();
-        const int64_t i = (round + gi) * kWave + gl;
-        if (i < g.m) prod[i] = static_cast<int64_t>(s_cnt[gi][gl]);
-        sch.done();
+    __shared__ int32_t s_end[kProdRows];
+    __shared__ unsigned long long s_cnt[kProdRows];
+    const int tid = threadIdx.x;
+    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kProdRows;
+    const int32_t rows = static_cast<int32_t>(g.m - r0 < kProdRows ? g.m - r0 : kProdRows);
+    for (int q = tid; q < kProdRows; q += 256) {
+        s_end[q] = g.a_ro[r0 + 1 + (q < rows ? q : rows - 1)];
+        s_cnt[q] = 0;
     }
+    const int32_t e0 = g.a_ro[r0];
+    __syncthreads();
+    const int32_t e1 = s_end[rows - 1];
+    constexpr int U = 4;  // entries in flight per thread
+    for (int64_t b = e0; b < e1; b += U * 256) {  // uniform across the block
+        int32_t len[U], row[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t e = b + tid + u * 256;
+            len[u] = -1;
+            if (e < e1) {
+                const int32_t j = g.a_ci[e];
+                len[u] = g.b_ro[j + 1] - g.b_ro[j];
+            }
+            row[u] = 0;  // the first row whose end is past e
+        }
+#pragma unroll
+        for (int step = kProdRows / 2; step > 0; step >>= 1) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (s_end[row[u] + step - 1] <= b + tid + u * 256) row[u] += step;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (len[u] > 0) atomicAdd(s_cnt + row[u], static_cast<unsigned long long>(len[u]));
+    }
+    __syncthreads();
+    for (int q = tid; q < rows; q += 256) prod[r0 + q] = static_cast<int64_t>(s_cnt[q]);
 }
 
 // Rows into their tier's list.  A block takes kClassRows consecutive rows
@@ -136,23 +140,26 @@ __global__ __launch_bounds__(256) void gemm_products(gemm_args g, int64_t *__res
 // reserves its stretch of each list with one atomicAdd per tier, and writes
 // each wavefront's rows from its own offset in that stretch.  (One atomic per
 // wavefront and tier put ~16k atomics on the one counter of a 1M-row
-// matrix whose rows share a tier, ~200 µs of serialized atomics.)
-constexpr int kClassRows = 1024;
+// matrix whose rows share a tier, ~200 µs of serialized atomics; blocks of 1024
+// rows still 17 µs.)
+constexpr int kClassRows = 4096;
+constexpr int kClassBlock = 1024;
+constexpr int kClassWaves = kClassBlock / kWave;
 
 __device__ __forceinline__ int gemm_tier_of(int64_t p, int32_t n) {
     if (p <= kTier0) return p < 0 ? -1 : (n < (1 << kTier0Bits) ? 3 : 0);
     return p <= kTier1 ? 0 : (p <= kTier2 ? 1 : 2);
 }
 
-__global__ __launch_bounds__(256) void gemm_classify(gemm_args g) {
-    __shared__ int32_t s_cnt[4][4];  // [wavefront][list]
+__global__ __launch_bounds__(kClassBlock) void gemm_classify(gemm_args g) {
+    __shared__ int32_t s_cnt[kClassWaves][4];  // [wavefront][list]
     __shared__ int32_t s_base[4];
     const int w = wave_id(), lane = lane_id();
     const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kClassRows;
     const int64_t r1 = r0 + kClassRows < g.m ? r0 + kClassRows : g.m;
     // pass 1: this wavefront's rows per list (list t holds tier t + 1 for t < 3, tier 0 for t = 3)
     int32_t cnt[4] = {0, 0, 0, 0};
-    for (int64_t i0 = r0 + w * kWave; i0 < r1; i0 += 256) {  // uniform per wavefront
+    for (int64_t i0 = r0 + w * kWave; i0 < r1; i0 += kClassBlock) {  // uniform per wavefront
         const int64_t i = i0 + lane;
         const int t = gemm_tier_of(i < r1 ? g.prod[i] : -1, g.n);
 #pragma unroll
@@ -163,7 +170,8 @@ __global__ __launch_bounds__(256) void gemm_classify(gemm_args g) {
     __syncthreads();
     if (threadIdx.x < 4) {
         const int q = threadIdx.x;
-        const int32_t total = s_cnt[0][q] + s_cnt[1][q] + s_cnt[2][q] + s_cnt[3][q];
+        int32_t total = 0;
+        for (int v = 0; v < kClassWaves; ++v) total += s_cnt[v][q];
         s_base[q] = total > 0 ? atomicAdd(g.list_len + (q == 3 ? 4 : q), total) : 0;
     }
     __syncthreads();
@@ -174,7 +182,7 @@ __global__ __launch_bounds__(256) void gemm_classify(gemm_args g) {
         off[q] = s_base[q];
         for (int v = 0; v < w; ++v) off[q] += s_cnt[v][q];
     }
-    for (int64_t i0 = r0 + w * kWave; i0 < r1; i0 += 256) {
+    for (int64_t i0 = r0 + w * kWave; i0 < r1; i0 += kClassBlock) {
         const int64_t i = i0 + lane;
         const int t = gemm_tier_of(i < r1 ? g.prod[i] : -1, g.n);
 #pragma unroll
@@ -748,9 +756,8 @@ static hipError_t gemm_pass(const spgemm_dev &P, int32_t *c_ro, int32_t *c_ci, f
         prof_scope p(s, "spgemm_products");
         // short rows (fewer than 8 entries on average) share wavefronts; longer ones get one each
         if (P.m > 0 && static_cast<int64_t>(P.a_nnz) < 8 * static_cast<int64_t>(P.m)) {
-            constexpr int RPB = group_block<kWave>::BLOCK;  // rows per block round: 4 groups of 64
-            hipLaunchKernelGGL(gemm_products, dim3(static_cast<uint32_t>(capped(P.m, RPB))), dim3(256), 0, s, g,
-                               w.prod);
+            const int64_t blocks = (static_cast<int64_t>(P.m) + kProdRows - 1) / kProdRows;
+            hipLaunchKernelGGL(gemm_products, dim3(static_cast<uint32_t>(blocks)), dim3(256), 0, s, g, w.prod);
         } else {
             constexpr int GPB = group_block<kWave>::GPB;  // grid-stride: at most 2^16 blocks
             const int64_t want = (static_cast<int64_t>(P.m) + GPB - 1) / GPB;
@@ -758,7 +765,7 @@ static hipError_t gemm_pass(const spgemm_dev &P, int32_t *c_ro, int32_t *c_ci, f
                                0, s, g, w.prod);
         }
         const int64_t cb = (static_cast<int64_t>(P.m) + kClassRows - 1) / kClassRows;
-        hipLaunchKernelGGL(gemm_classify, dim3(static_cast<uint32_t>(cb < 1 ? 1 : cb)), dim3(256), 0, s, g);
+        hipLaunchKernelGGL(gemm_classify, dim3(static_cast<uint32_t>(cb < 1 ? 1 : cb)), dim3(kClassBlock), 0, s, g);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
