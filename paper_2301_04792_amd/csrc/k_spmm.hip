@@ -316,10 +316,19 @@ __global__ __launch_bounds__(BLOCK) void merge_spmm_rows(
         }
         const int32_t it0 = lo, it1 = lo1, jt1 = dend - lo1;
 
-        float acc[V], first_sum[V];
+        // a row's products are summed in fours (part, half), the pairs of fours in
+        // acc: a group's chain is otherwise ITEMS << lg additions long and rounds worse
+        float acc[V], part[V], half[V], first_sum[V];
 #pragma unroll
-        for (int c = 0; c < V; ++c) acc[c] = first_sum[c] = 0.f;
+        for (int c = 0; c < V; ++c) acc[c] = part[c] = half[c] = first_sum[c] = 0.f;
         int32_t it = it0;
+        auto fold = [&]() {
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+                acc[c] += half[c] + part[c];
+                half[c] = part[c] = 0.f;
+            }
+        };
         auto close_row = [&]() {
             if (it == it0) {  // waits for the earlier groups' part
 #pragma unroll
@@ -343,15 +352,24 @@ __global__ __launch_bounds__(BLOCK) void merge_spmm_rows(
             }
 #pragma unroll
             for (int a = 0; a < kAhead; ++a) {
+                if (a == kAhead / 2) {
+#pragma unroll
+                    for (int c = 0; c < V; ++c) {
+                        half[c] = part[c];
+                        part[c] = 0.f;
+                    }
+                }
                 if (j + a < jt1) {
                     while (end <= j + a) {
+                        fold();
                         close_row();
                         end = it < it1 ? s_re[it] : INT32_MAX;
                     }
 #pragma unroll
-                    for (int c = 0; c < V; ++c) acc[c] += v[a] * g[a][c];
+                    for (int c = 0; c < V; ++c) part[c] += v[a] * g[a][c];
                 }
             }
+            fold();
         }
         while (it < it1) close_row();
 
