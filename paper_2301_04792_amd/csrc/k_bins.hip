@@ -102,9 +102,11 @@ __global__ __launch_bounds__(kBinBlock) void bin_products(
     const float *__restrict__ dy, float *__restrict__ dvalues, const int32_t *__restrict__ part_i,
     const int32_t *__restrict__ part_j, int32_t *__restrict__ start, float *__restrict__ prod,
     uint16_t *__restrict__ key, float *__restrict__ out, bool windows) {
-    // row ends and row labels, then the products in bin order; columns in bin order
-    __shared__ int32_t s_buf[kBinW];
-    __shared__ int32_t s_col[kBinW];
+    // row ends and row labels, then the products in bin order; columns in bin
+    // order.  In their place: the float64 sums of a window
+    __shared__ double s_win[kBinW];
+    int32_t *s_buf = reinterpret_cast<int32_t *>(s_win);
+    int32_t *s_col = s_buf + kBinW;
     __shared__ int32_t s_cnt[kBinMax], s_start[kBinMax];
     __shared__ int32_t s_wave[kBinBlock / kWave];
     __shared__ int32_t s_lo[kBinBlock / kWave], s_hi[kBinBlock / kWave];
@@ -220,18 +222,18 @@ __global__ __launch_bounds__(kBinBlock) void bin_products(
         }
     }
     if (window) {  // sum them here
-        float *s_win = reinterpret_cast<float *>(s_col);
+        __syncthreads();  // the labels have been read
         const int32_t width = cmax - cmin + 1;
-        for (int32_t c = tid; c < width; c += kBinBlock) s_win[c] = 0.f;
+        for (int32_t c = tid; c < width; c += kBinBlock) s_win[c] = 0.0;
         if (tid < nb) start[static_cast<int64_t>(b) * (nb + 1) + tid] = 0;
         if (tid == 0) start[static_cast<int64_t>(b) * (nb + 1) + nb] = 0;
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < kBinItems; ++u)
-            if (tid + u * kBinBlock < nnzs) unsafeAtomicAdd(s_win + (cc[u] - cmin), pr[u]);
+            if (tid + u * kBinBlock < nnzs) unsafeAtomicAdd(s_win + (cc[u] - cmin), static_cast<double>(pr[u]));
         __syncthreads();
         for (int32_t c = tid; c < width; c += kBinBlock) {
-            const float v = s_win[c];
+            const float v = static_cast<float>(s_win[c]);
             if (v != 0.f) unsafeAtomicAdd(out + cmin + c, v);
         }
         return;
