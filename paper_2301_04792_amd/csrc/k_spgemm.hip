@@ -11,9 +11,9 @@
 //                           sorted in registers;
 //   tier 1 (p_i <= 256):   one wavefront per row; the products, keyed by
 //                           (column, product index), are bitonic-sorted in
-//                           the wavefront's LDS; equal columns are then
-//                           adjacent, in product order;
-//   tier 2 (p_i <= 4096):  one block per row, the same in block LDS;
+//                           registers; equal columns are then adjacent, in
+//                           product order;
+//   tier 2 (p_i <= 4096):  one block per row, the same;
 //   tier 3 (larger):       blocks of a work queue (32 to 512, as many as
 //                           1 GiB of slots holds), each owning a slot of
 //                           global memory with a dense float accumulator
@@ -41,7 +41,6 @@ constexpr int kTier1 = 256;
 constexpr int kTier2 = 4096;
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / kWave;
-constexpr uint64_t kPad = ~0ull;  // sorts after every real key
 
 struct gemm_args {
     int32_t m, n;
@@ -64,12 +63,6 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ int32_t next_pow2(int32_t v) {
-    int32_t p = 1;
-    while (p < v) p <<= 1;
-    return p;
 }
 
 // ---------------------------------------------------------------- products per row and tiers
@@ -196,33 +189,7 @@ __global__ __launch_bounds__(kClassBlock) void gemm_classify(gemm_args g) {
     }
 }
 
-// ---------------------------------------------------------------- tiers 1 and 2: sort in LDS
-
-// Bitonic sort of key[0, np2) (np2 a power of two) with its values, by
-// threads [t0, t0 + nt) of the block; sync() orders LDS between steps.
-template <bool VALUES, typename Sync>
-__device__ __forceinline__ void lds_bitonic(uint64_t *key, float *val, int32_t np2, int t, int nt, Sync sync) {
-    for (int32_t k = 2; k <= np2; k <<= 1) {
-        for (int32_t j = k >> 1; j > 0; j >>= 1) {
-            for (int32_t x = t; x < np2 / 2; x += nt) {
-                const int32_t lo = 2 * j * (x / j) + (x % j);
-                const int32_t hi = lo + j;
-                const bool up = (lo & k) == 0;
-                const uint64_t a = key[lo], b = key[hi];
-                if ((a > b) == up) {
-                    key[lo] = b;
-                    key[hi] = a;
-                    if constexpr (VALUES) {
-                        const float va = val[lo];
-                        val[lo] = val[hi];
-                        val[hi] = va;
-                    }
-                }
-            }
-            sync();
-        }
-    }
-}
+// ---------------------------------------------------------------- tiers 0, 1 and 2: sort in registers
 
 // Exchange with lane gl ^ D of an aligned group of eight lanes (DPP: no LDS).
 template <int D>
@@ -377,152 +344,287 @@ __global__ __launch_bounds__(kBlock) void gemm_tier0(gemm_args g) {
     }
 }
 
-// Tier 1: a wavefront per row.
-template <bool COMPUTE>
-__global__ __launch_bounds__(kBlock) void gemm_tier1(gemm_args g) {
-    __shared__ uint64_t s_key[kWavesPerBlock][kTier1];
-    __shared__ float s_val[kWavesPerBlock][COMPUTE ? kTier1 : 1];
-    const int lane = lane_id(), w = wave_id();
-    uint64_t *key = s_key[w];
-    float *val = s_val[w];
-    const int32_t rows = g.list_len[0];
-    const int64_t waves = static_cast<int64_t>(gridDim.x) * kWavesPerBlock;
-    for (int64_t r = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + w; r < rows; r += waves) {
-        const int32_t i = g.lists[r];
-        const int32_t p = static_cast<int32_t>(g.prod[i]);
-        const int32_t a0 = g.a_ro[i], a1 = g.a_ro[i + 1];
-        // expand: 64 A entries at a time; lane l writes its entry's products
-        int32_t base = 0;
-        for (int32_t c0 = a0; c0 < a1; c0 += kWave) {
-            const int32_t e = c0 + lane;
-            int32_t j = 0, len = 0;
-            if (e < a1) {
-                j = g.a_ci[e];
-                len = g.b_ro[j + 1] - g.b_ro[j];
-            }
-            const int32_t incl = group_scan_incl<kWave>(len);
-            const int32_t start = base + incl - len;
-            if (len > 0) {
-                const int32_t f0 = g.b_ro[j];
-                const float a = COMPUTE ? g.a_val[e] : 0.f;
-                for (int32_t t = 0; t < len; ++t) {
-                    const int32_t q = start + t;
-                    key[q] = (static_cast<uint64_t>(g.b_ci[f0 + t]) << 32) | static_cast<uint32_t>(q);
-                    if constexpr (COMPUTE) val[q] = a * g.b_val[f0 + t];
+// Exchange with lane ^ D of the wavefront.
+__device__ __forceinline__ uint32_t lane_swap(uint32_t v, int d) {  // d is a constant where it is called
+    switch (d) {
+        case 1: return swap8<1>(v);
+        case 2: return swap8<2>(v);
+        case 4: return swap8<4>(v);
+        case 8:  // row_ror:8
+            return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x128, 0xF, 0xF, false));
+        default: return __shfl_xor(v, d, kWave);
+    }
+}
+__device__ __forceinline__ uint64_t lane_swap(uint64_t v, int d) {
+    return static_cast<uint64_t>(lane_swap(static_cast<uint32_t>(v >> 32), d)) << 32 |
+           lane_swap(static_cast<uint32_t>(v), d);
+}
+
+// The threads of one row: a wavefront or a block.
+template <int T>
+struct row_team {
+    static __device__ __forceinline__ int rank() { return threadIdx.x & (T - 1); }
+    static __device__ __forceinline__ void sync() {
+        if constexpr (T == kWave)
+            wave_sync();
+        else
+            __syncthreads();
+    }
+    static __device__ __forceinline__ int32_t scan_incl(int32_t v, int32_t *s_wave) {
+        if constexpr (T == kWave)
+            return group_scan_incl<kWave>(v);
+        else
+            return block_scan_incl<T>(v, s_wave);
+    }
+    static __device__ __forceinline__ float open_sum(seg_t x, seg_t *s_wave) {  // exclusive segmented scan
+        if constexpr (T == kWave) {
+            const seg_t incl = group_seg_scan_incl<kWave>(x);
+            const float v = __shfl_up(incl.v, 1, kWave);
+            return rank() ? v : 0.f;
+        } else {
+            seg_t tot;
+            return block_seg_scan_excl<T>(x, s_wave, tot).v;
+        }
+    }
+};
+
+// LDS of one row of at most P products on T threads.
+template <int T, int P, typename K, bool COMPUTE>
+struct row_lds {
+    K key[P];                        // keys in product order; then of the exchange; then the columns of C
+    float val[COMPUTE ? P : 1];      // products; then the values of C
+    int32_t start[T], from[T];       // first product of an A entry; its B row begins at from + start
+    float a[COMPUTE ? T : 1];
+    int32_t total;
+    int32_t wave[T / kWave];
+    seg_t seg[T / kWave];
+};
+
+// Ascending bitonic sort of T * E keys, thread t elements E t .. E t + E - 1:
+// distances below E are inside a thread, below 64 E lane exchanges, the rest go
+// through LDS (x, T * E keys).
+template <int T, int E, typename K>
+__device__ __forceinline__ void sort_keys(K (&k)[E], int t, K *x) {
+#pragma unroll
+    for (int size = 2; size <= T * E; size <<= 1) {
+#pragma unroll
+        for (int j = size >> 1; j > 0; j >>= 1) {
+            if (j >= E) {
+                const int d = j / E;
+                const bool keep_min = ((t & d) == 0) == ((t & (size / E)) == 0);
+                if (d >= kWave) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e) x[e * T + t] = k[e];
+                    row_team<T>::sync();
+                }
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const K o = d < kWave ? lane_swap(k[e], d) : x[e * T + (t ^ d)];
+                    k[e] = (k[e] < o) == keep_min ? k[e] : o;
+                }
+                if (d >= kWave) row_team<T>::sync();
+            } else {
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    if ((e & j) == 0) {
+                        const bool up = size < E ? (e & size) == 0 : (t & (size / E)) == 0;
+                        const K p = k[e], q = k[e | j];
+                        const bool keep = (p < q) == up;
+                        k[e] = keep ? p : q;
+                        k[e | j] = keep ? q : p;
+                    }
                 }
             }
-            base += __shfl(incl, kWave - 1);
         }
-        const int32_t np2 = next_pow2(p > 1 ? p : 1);
-        for (int32_t q = p + lane; q < np2; q += kWave) key[q] = kPad;
-        wave_sync();
-        lds_bitonic<COMPUTE>(key, val, np2, lane, kWave, wave_sync);
-        // runs of equal columns: count them, or sum each run and write it
-        int32_t rank = 0;  // columns written so far
-        float carry = 0.f; // open run's partial sum from earlier chunks
-        const int32_t out0 = COMPUTE ? g.c_ro[i] : 0;
-        for (int32_t c0 = 0; c0 < p; c0 += kWave) {
-            const int32_t q = c0 + lane;
-            const bool in = q < p;
-            const uint32_t col = in ? static_cast<uint32_t>(key[q] >> 32) : 0xffffffffu;
-            const uint32_t prev = q > 0 && in ? static_cast<uint32_t>(key[q - 1] >> 32) : 0xffffffffu;
-            const bool head = in && (q == 0 || col != prev);
-            const uint64_t hm = __ballot(head);
-            if constexpr (COMPUTE) {
-                const bool tail = in && (q == p - 1 || static_cast<uint32_t>(key[q + 1] >> 32) != col);
-                seg_t sv = group_seg_scan_incl<kWave>(seg_t{in ? val[q] : 0.f, head});
-                if (!sv.f) sv.v += carry;  // the run began in an earlier chunk
-                const int32_t my_rank = rank + __popcll(hm & ((2ull << lane) - 1)) - 1;
-                if (tail) {
-                    g.c_ci[out0 + my_rank] = static_cast<int32_t>(col);
-                    g.c_val[out0 + my_rank] = sv.v;
-                }
-                carry = __shfl(sv.v, kWave - 1);
-            }
-            rank += __popcll(hm);
-        }
-        if constexpr (!COMPUTE) {
-            if (lane == 0) g.c_ro[i] = rank;
-        }
-        wave_sync();
     }
 }
 
-// Tier 2: a block per row.
-template <bool COMPUTE>
-__global__ __launch_bounds__(kBlock) void gemm_tier2(gemm_args g) {
-    __shared__ uint64_t s_key[kTier2];
-    __shared__ float s_val[COMPUTE ? kTier2 : 1];
-    __shared__ int32_t s_wi[kBlock / kWave];
-    __shared__ seg_t s_ws[kBlock / kWave];
-    __shared__ int32_t s_int;
-    __shared__ float s_float;
-    const int tid = threadIdx.x;
-    const int32_t rows = g.list_len[1];
-    auto bsync = [] { __syncthreads(); };
-    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {  // uniform across the block
-        const int32_t i = g.lists[static_cast<int64_t>(g.m) + r];
+// The p products of a row, already in l.key (column << BITS | product) and l.val:
+// sorted, equal columns summed in product order, written from out0 (compute), or
+// the columns counted (returned by the last thread).
+template <int T, int P, int E, int BITS, typename K, bool COMPUTE>
+__device__ __forceinline__ int32_t reduce_row(const gemm_args &g, row_lds<T, P, K, COMPUTE> &l, int32_t p,
+                                              int32_t out0) {
+    using team = row_team<T>;
+    const int t = team::rank();
+    K k[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) k[e] = e * T + t < p ? l.key[e * T + t] : ~static_cast<K>(0);  // sorts last
+    team::sync();
+    sort_keys<T, E, K>(k, t, l.key);
+    // the neighbours' keys
+    l.key[t] = k[E - 1];
+    K before, after;
+    if constexpr (T == kWave) {
+        team::sync();
+        before = l.key[t ? t - 1 : 0];
+        team::sync();
+        l.key[t] = k[0];
+        team::sync();
+        after = l.key[t < T - 1 ? t + 1 : t];
+    } else {
+        l.key[T + t] = k[0];
+        team::sync();
+        before = l.key[t ? t - 1 : 0];
+        after = l.key[T + (t < T - 1 ? t + 1 : t)];
+    }
+    bool head[E + 1];  // of a run of equal columns
+    int32_t cnt = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const K last = e ? k[e ? e - 1 : 0] : before;
+        head[e] = E * t + e < p && (E * t + e == 0 || (k[e] >> BITS) != (last >> BITS));
+        cnt += head[e] ? 1 : 0;
+    }
+    head[E] = E * t + E >= p || (after >> BITS) != (k[E - 1] >> BITS);
+    const int32_t upto = team::scan_incl(cnt, l.wave);
+    if constexpr (COMPUTE) {
+        float v[E];
+        seg_t mine{0.f, 0};
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const bool in = E * t + e < p;
+            v[e] = in ? l.val[static_cast<uint32_t>(k[e]) & ((1u << BITS) - 1)] : 0.f;
+            mine = head[e] ? seg_t{v[e], 1} : seg_t{mine.v + v[e], mine.f};
+        }
+        float sum = team::open_sum(mine, l.seg);
+        if (t == T - 1) l.total = upto;
+        team::sync();  // keys and products have been read: C's entries take their place
+        int32_t at = upto - cnt - 1;
+        uint32_t *col = reinterpret_cast<uint32_t *>(l.key);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            sum = head[e] ? v[e] : sum + v[e];
+            at += head[e] ? 1 : 0;
+            if (E * t + e < p && (E * t + e == p - 1 || head[e + 1])) {
+                col[at] = static_cast<uint32_t>(k[e] >> BITS);
+                l.val[at] = sum;
+            }
+        }
+        team::sync();
+        const int32_t total = l.total;
+        for (int32_t q = t; q < total; q += T) {
+            g.c_ci[out0 + q] = static_cast<int32_t>(col[q]);
+            g.c_val[out0 + q] = l.val[q];
+        }
+    }
+    return upto;
+}
+
+// Tiers 1 (a wavefront per row, up to 256 products) and 2 (a block per row, up to
+// 4096).  The products of T entries of A at a time are dealt to the threads in
+// order, each finding its entry among the starts in LDS, so B rows are read
+// coalesced whatever their lengths; they are sorted in registers by (column,
+// product index), which fits 32 bits where C has at most 2^(32 - BITS) columns
+// (K), and a value is fetched by its product index once its place is known.
+// 50,378 power-law rows squared: block rows 67 us to compute and 50 to count,
+// wavefront rows 12 and 10; 50,000 rows of 1 to 32 entries: 257, 154, 37 and 29.
+// (An LDS network of 64-bit keys and values, expanded by a thread per B row, took
+// 600, 494, 55 and 40; 911, 534, 126 and 89.)
+template <int T, int P, int BITS, typename K, bool COMPUTE>
+__global__ __launch_bounds__(kBlock) void gemm_sort_rows(gemm_args g, const int32_t *__restrict__ list,
+                                                         const int32_t *__restrict__ len) {
+    using team = row_team<T>;
+    constexpr int PER = kBlock / T;  // rows of a block
+    __shared__ row_lds<T, P, K, COMPUTE> s_row[PER];
+    const int t = team::rank();
+    row_lds<T, P, K, COMPUTE> &l = s_row[threadIdx.x / T];
+    const int32_t rows = *len;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * PER;
+    for (int64_t r = static_cast<int64_t>(blockIdx.x) * PER + threadIdx.x / T; r < rows; r += step) {  // uniform in the team
+        const int32_t i = list[r];
         const int32_t p = static_cast<int32_t>(g.prod[i]);
         const int32_t a0 = g.a_ro[i], a1 = g.a_ro[i + 1];
         int32_t base = 0;
-        for (int32_t c0 = a0; c0 < a1; c0 += kBlock) {
-            const int32_t e = c0 + tid;
-            int32_t j = 0, len = 0;
+        for (int32_t c0 = a0; c0 < a1; c0 += T) {
+            const int32_t e = c0 + t;
+            int32_t f0 = 0, n = 0;
+            float a = 0.f;
             if (e < a1) {
-                j = g.a_ci[e];
-                len = g.b_ro[j + 1] - g.b_ro[j];
+                const int32_t j = g.a_ci[e];
+                if constexpr (COMPUTE) a = g.a_val[e];
+                f0 = g.b_ro[j];
+                n = g.b_ro[j + 1] - f0;
             }
-            const int32_t incl = block_scan_incl<kBlock>(len, s_wi);
-            const int32_t start = base + incl - len;
-            if (len > 0) {
-                const int32_t f0 = g.b_ro[j];
-                const float a = COMPUTE ? g.a_val[e] : 0.f;
-                for (int32_t t = 0; t < len; ++t) {
-                    const int32_t q = start + t;
-                    s_key[q] = (static_cast<uint64_t>(g.b_ci[f0 + t]) << 32) | static_cast<uint32_t>(q);
-                    if constexpr (COMPUTE) s_val[q] = a * g.b_val[f0 + t];
+            const int32_t incl = team::scan_incl(n, l.wave);
+            const int32_t first = base + incl - n;
+            l.start[t] = first;
+            l.from[t] = f0 - first;
+            if constexpr (COMPUTE) l.a[t] = a;
+            if (t == T - 1) l.total = base + incl;
+            team::sync();
+            const int32_t end = l.total;
+            constexpr int U = 4;  // products in flight per thread
+            for (int32_t q0 = base + t; q0 < end; q0 += U * T) {
+                int32_t q[U], w[U], c[U];
+                float b[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    q[u] = q0 + u * T < end ? q0 + u * T : end - 1;
+                    w[u] = 0;
+                }
+#pragma unroll
+                for (int s = T / 2; s > 0; s >>= 1) {  // the last entry that starts at or before q
+#pragma unroll
+                    for (int u = 0; u < U; ++u) w[u] += l.start[w[u] + s] <= q[u] ? s : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int32_t f = l.from[w[u]] + q[u];
+                    c[u] = g.b_ci[f];
+                    if constexpr (COMPUTE) b[u] = g.b_val[f];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (q0 + u * T < end) {
+                        l.key[q[u]] = static_cast<K>(c[u]) << BITS | static_cast<uint32_t>(q[u]);
+                        if constexpr (COMPUTE) l.val[q[u]] = l.a[w[u]] * b[u];
+                    }
                 }
             }
-            if (tid == kBlock - 1) s_int = incl;
-            __syncthreads();
-            base += s_int;
-            __syncthreads();
+            base = end;
+            team::sync();
         }
-        const int32_t np2 = next_pow2(p > 1 ? p : 1);
-        for (int32_t q = p + tid; q < np2; q += kBlock) s_key[q] = kPad;
-        __syncthreads();
-        lds_bitonic<COMPUTE>(s_key, s_val, np2, tid, kBlock, bsync);
-        int32_t rank = 0;
-        float carry = 0.f;
         const int32_t out0 = COMPUTE ? g.c_ro[i] : 0;
-        for (int32_t c0 = 0; c0 < p; c0 += kBlock) {  // uniform across the block
-            const int32_t q = c0 + tid;
-            const bool in = q < p;
-            const uint32_t col = in ? static_cast<uint32_t>(s_key[q] >> 32) : 0xffffffffu;
-            const uint32_t prev = q > 0 && in ? static_cast<uint32_t>(s_key[q - 1] >> 32) : 0xffffffffu;
-            const bool head = in && (q == 0 || col != prev);
-            const int32_t hincl = block_scan_incl<kBlock>(head ? 1 : 0, s_wi);
-            if constexpr (COMPUTE) {
-                const bool tail = in && (q == p - 1 || static_cast<uint32_t>(s_key[q + 1] >> 32) != col);
-                seg_t tot;
-                seg_t sv = block_seg_scan_incl<kBlock>(seg_t{in ? s_val[q] : 0.f, head}, s_ws, tot);
-                if (!sv.f) sv.v += carry;
-                if (tail) {
-                    g.c_ci[out0 + rank + hincl - 1] = static_cast<int32_t>(col);
-                    g.c_val[out0 + rank + hincl - 1] = sv.v;
-                }
-                if (tid == kBlock - 1) s_float = sv.v;
-            }
-            if (tid == kBlock - 1) s_int = hincl;
-            __syncthreads();
-            rank += s_int;
-            if constexpr (COMPUTE) carry = s_float;
-            __syncthreads();
+        int32_t upto;  // the smallest network that holds the products
+        if constexpr (T == kWave) {
+            if (p <= T)
+                upto = reduce_row<T, P, 1, BITS, K, COMPUTE>(g, l, p, out0);
+            else if (p <= 2 * T)
+                upto = reduce_row<T, P, 2, BITS, K, COMPUTE>(g, l, p, out0);
+            else
+                upto = reduce_row<T, P, 4, BITS, K, COMPUTE>(g, l, p, out0);
+        } else {
+            if (p <= 2 * T)
+                upto = reduce_row<T, P, 2, BITS, K, COMPUTE>(g, l, p, out0);
+            else if (p <= 4 * T)
+                upto = reduce_row<T, P, 4, BITS, K, COMPUTE>(g, l, p, out0);
+            else if (p <= 8 * T)
+                upto = reduce_row<T, P, 8, BITS, K, COMPUTE>(g, l, p, out0);
+            else
+                upto = reduce_row<T, P, 16, BITS, K, COMPUTE>(g, l, p, out0);
         }
         if constexpr (!COMPUTE) {
-            if (tid == 0) g.c_ro[i] = rank;
+            if (t == T - 1) g.c_ro[i] = upto;
         }
-        __syncthreads();
+        team::sync();
+    }
+}
+
+template <int T, int P, int BITS>
+void sort_rows(const gemm_args &g, const int32_t *list, const int32_t *len, uint32_t grid, bool compute,
+               hipStream_t s) {
+    const bool narrow = g.n <= (1ll << (32 - BITS));
+    if (compute) {
+        if (narrow)
+            hipLaunchKernelGGL((gemm_sort_rows<T, P, BITS, uint32_t, true>), dim3(grid), dim3(kBlock), 0, s, g, list, len);
+        else
+            hipLaunchKernelGGL((gemm_sort_rows<T, P, BITS, uint64_t, true>), dim3(grid), dim3(kBlock), 0, s, g, list, len);
+    } else {
+        if (narrow)
+            hipLaunchKernelGGL((gemm_sort_rows<T, P, BITS, uint32_t, false>), dim3(grid), dim3(kBlock), 0, s, g, list, len);
+        else
+            hipLaunchKernelGGL((gemm_sort_rows<T, P, BITS, uint64_t, false>), dim3(grid), dim3(kBlock), 0, s, g, list, len);
     }
 }
 
@@ -788,17 +890,11 @@ static hipError_t gemm_pass(const spgemm_dev &P, int32_t *c_ro, int32_t *c_ci, f
     }
     {
         prof_scope p(s, names[c][1]);
-        if (compute)
-            hipLaunchKernelGGL(gemm_tier1<true>, dim3(grid12), dim3(kBlock), 0, s, g);
-        else
-            hipLaunchKernelGGL(gemm_tier1<false>, dim3(grid12), dim3(kBlock), 0, s, g);
+        sort_rows<kWave, kTier1, 8>(g, w.lists, w.list_len, grid12, compute, s);
     }
     {
         prof_scope p(s, names[c][2]);
-        if (compute)
-            hipLaunchKernelGGL(gemm_tier2<true>, dim3(grid12), dim3(kBlock), 0, s, g);
-        else
-            hipLaunchKernelGGL(gemm_tier2<false>, dim3(grid12), dim3(kBlock), 0, s, g);
+        sort_rows<kBlock, kTier2, 12>(g, w.lists + P.m, w.list_len + 1, grid12, compute, s);
     }
     {
         prof_scope p(s, names[c][3]);
