@@ -14,14 +14,15 @@
 //                           registers; equal columns are then adjacent, in
 //                           product order;
 //   tier 2 (p_i <= 4096):  one block per row, the same;
-//   tier 3 (larger):       blocks of a work queue (32 to 512, as many as
-//                           1 GiB of slots holds), each owning a slot of
-//                           global memory with a dense float accumulator
-//                           and a two-level column bitmap; products are
-//                           enumerated by the group_mapped_scan schedule
-//                           over the row's A entries (tiles) and their B
-//                           rows (atoms); the columns come out ascending by
-//                           walking the bitmap.
+//   tier 3 (larger):       blocks of a work queue (32 to 512), a row at a time:
+//                           a column bitmap gives the columns in order, and the
+//                           products are added by column.  Up to 2^18 columns
+//                           the bitmap and the sums are in LDS; beyond, each
+//                           block owns a slot of global memory (1 GiB in all)
+//                           with a dense float accumulator and a two-level
+//                           bitmap, and the products are enumerated by the
+//                           group_mapped_scan schedule over the row's A
+//                           entries (tiles) and their B rows (atoms).
 // The count pass runs the same tiers without values and writes each row's
 // column count; an int64 scan turns them into C's row offsets.  Tiers 1 and
 // 2 sum each column's products in product order (deterministic); tier 3
@@ -40,7 +41,11 @@ constexpr int kTier0Bits = 27;  // C's columns fit this many bits (wider ones: t
 constexpr int kTier1 = 256;
 constexpr int kTier2 = 4096;
 constexpr int kBlock = 256;
-constexpr int kWavesPerBlock = kBlock / kWave;
+constexpr int kBitBlock = 1024;
+constexpr int kBitChunk = 16 * kBitBlock;  // columns emitted together, 16 a thread
+constexpr int64_t kBitCols = 1 << 18;
+constexpr int kBitSums = 1 << 14;  // entries of C summed together
+constexpr int kBitPasses = 4;
 
 struct gemm_args {
     int32_t m, n;
@@ -388,15 +393,86 @@ struct row_team {
     }
 };
 
+// The products of a row dealt to T threads: EN entries of A at a time.
+template <int T, int EN, bool COMPUTE>
+struct row_deal {
+    int32_t start[EN], from[EN];  // first product of an A entry; its B row begins at from + start
+    float a[COMPUTE ? EN : 1];
+    int32_t total;
+    int32_t wave[T / kWave];
+};
+
+// Calls body(q, column of B, product) for every product q of the entries [a0, a1)
+// of A.  The products of EN entries are dealt to the threads in order, each
+// finding its entry among the starts in LDS, so B rows are read coalesced whatever
+// their lengths.  Every thread of the team calls it; the LDS is free afterwards.
+// q is exact up to 2^32 products; without VALUES the product is 0.
+template <bool VALUES, int T, int EN, bool COMPUTE, typename F>
+__device__ __forceinline__ void each_product(const gemm_args &g, row_deal<T, EN, COMPUTE> &l, int32_t a0, int32_t a1,
+                                             F body) {
+    using team = row_team<T>;
+    const int t = team::rank();
+    uint32_t base = 0;
+    for (int32_t c0 = a0; c0 < a1; c0 += EN) {
+        const int32_t e = c0 + t;
+        int32_t f0 = 0, n = 0;
+        float a = 0.f;
+        if (t < EN && e < a1) {
+            const int32_t j = g.a_ci[e];
+            if constexpr (VALUES) a = g.a_val[e];
+            f0 = g.b_ro[j];
+            n = g.b_ro[j + 1] - f0;
+        }
+        const int32_t incl = team::scan_incl(n, l.wave);
+        if (t < EN) {
+            l.start[t] = incl - n;
+            l.from[t] = f0 - (incl - n);
+            if constexpr (VALUES) l.a[t] = a;
+        }
+        if (t == T - 1) l.total = incl;
+        team::sync();
+        const uint32_t end = l.total;
+        constexpr int U = 4;  // products in flight per thread
+        for (uint32_t q0 = t; q0 < end; q0 += U * T) {
+            int32_t q[U], w[U], c[U];
+            float b[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                q[u] = static_cast<int32_t>(q0 + u * T < end ? q0 + u * T : end - 1);
+                w[u] = 0;
+            }
+#pragma unroll
+            for (int s = EN / 2; s > 0; s >>= 1) {  // the last entry that starts at or before q
+#pragma unroll
+                for (int u = 0; u < U; ++u) w[u] += l.start[w[u] + s] <= q[u] ? s : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t f = l.from[w[u]] + q[u];
+                c[u] = g.b_ci[f];
+                if constexpr (VALUES) b[u] = g.b_val[f];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (q0 + u * T < end) {
+                    if constexpr (VALUES)
+                        body(base + q[u], c[u], l.a[w[u]] * b[u]);
+                    else
+                        body(base + q[u], c[u], 0.f);
+                }
+            }
+        }
+        base += end;
+        team::sync();
+    }
+}
+
 // LDS of one row of at most P products on T threads.
 template <int T, int P, typename K, bool COMPUTE>
 struct row_lds {
-    K key[P];                        // keys in product order; then of the exchange; then the columns of C
-    float val[COMPUTE ? P : 1];      // products; then the values of C
-    int32_t start[T], from[T];       // first product of an A entry; its B row begins at from + start
-    float a[COMPUTE ? T : 1];
-    int32_t total;
-    int32_t wave[T / kWave];
+    K key[P];                    // keys in product order; then of the exchange; then the columns of C
+    float val[COMPUTE ? P : 1];  // products; then the values of C
+    row_deal<T, T, COMPUTE> deal;
     seg_t seg[T / kWave];
 };
 
@@ -477,7 +553,7 @@ __device__ __forceinline__ int32_t reduce_row(const gemm_args &g, row_lds<T, P, 
         cnt += head[e] ? 1 : 0;
     }
     head[E] = E * t + E >= p || (after >> BITS) != (k[E - 1] >> BITS);
-    const int32_t upto = team::scan_incl(cnt, l.wave);
+    const int32_t upto = team::scan_incl(cnt, l.deal.wave);
     if constexpr (COMPUTE) {
         float v[E];
         seg_t mine{0.f, 0};
@@ -488,7 +564,7 @@ __device__ __forceinline__ int32_t reduce_row(const gemm_args &g, row_lds<T, P, 
             mine = head[e] ? seg_t{v[e], 1} : seg_t{mine.v + v[e], mine.f};
         }
         float sum = team::open_sum(mine, l.seg);
-        if (t == T - 1) l.total = upto;
+        if (t == T - 1) l.deal.total = upto;
         team::sync();  // keys and products have been read: C's entries take their place
         int32_t at = upto - cnt - 1;
         uint32_t *col = reinterpret_cast<uint32_t *>(l.key);
@@ -502,7 +578,7 @@ __device__ __forceinline__ int32_t reduce_row(const gemm_args &g, row_lds<T, P, 
             }
         }
         team::sync();
-        const int32_t total = l.total;
+        const int32_t total = l.deal.total;
         for (int32_t q = t; q < total; q += T) {
             g.c_ci[out0 + q] = static_cast<int32_t>(col[q]);
             g.c_val[out0 + q] = l.val[q];
@@ -512,15 +588,13 @@ __device__ __forceinline__ int32_t reduce_row(const gemm_args &g, row_lds<T, P, 
 }
 
 // Tiers 1 (a wavefront per row, up to 256 products) and 2 (a block per row, up to
-// 4096).  The products of T entries of A at a time are dealt to the threads in
-// order, each finding its entry among the starts in LDS, so B rows are read
-// coalesced whatever their lengths; they are sorted in registers by (column,
-// product index), which fits 32 bits where C has at most 2^(32 - BITS) columns
-// (K), and a value is fetched by its product index once its place is known.
-// 50,378 power-law rows squared: block rows 67 us to compute and 50 to count,
-// wavefront rows 12 and 10; 50,000 rows of 1 to 32 entries: 257, 154, 37 and 29.
-// (An LDS network of 64-bit keys and values, expanded by a thread per B row, took
-// 600, 494, 55 and 40; 911, 534, 126 and 89.)
+// 4096).  The products are sorted in registers by (column, product index), which
+// fits 32 bits where C has at most 2^(32 - BITS) columns (K), and a value is
+// fetched by its product index once its place is known.  50,378 power-law rows
+// squared: block rows 67 us to compute and 50 to count, wavefront rows 12 and 10;
+// 50,000 rows of 1 to 32 entries: 257, 154, 37 and 29.  (An LDS network of
+// 64-bit keys and values, expanded by a thread per B row, took 600, 494, 55 and
+// 40; 911, 534, 126 and 89.)
 template <int T, int P, int BITS, typename K, bool COMPUTE>
 __global__ __launch_bounds__(kBlock) void gemm_sort_rows(gemm_args g, const int32_t *__restrict__ list,
                                                          const int32_t *__restrict__ len) {
@@ -535,56 +609,10 @@ __global__ __launch_bounds__(kBlock) void gemm_sort_rows(gemm_args g, const int3
         const int32_t i = list[r];
         const int32_t p = static_cast<int32_t>(g.prod[i]);
         const int32_t a0 = g.a_ro[i], a1 = g.a_ro[i + 1];
-        int32_t base = 0;
-        for (int32_t c0 = a0; c0 < a1; c0 += T) {
-            const int32_t e = c0 + t;
-            int32_t f0 = 0, n = 0;
-            float a = 0.f;
-            if (e < a1) {
-                const int32_t j = g.a_ci[e];
-                if constexpr (COMPUTE) a = g.a_val[e];
-                f0 = g.b_ro[j];
-                n = g.b_ro[j + 1] - f0;
-            }
-            const int32_t incl = team::scan_incl(n, l.wave);
-            const int32_t first = base + incl - n;
-            l.start[t] = first;
-            l.from[t] = f0 - first;
-            if constexpr (COMPUTE) l.a[t] = a;
-            if (t == T - 1) l.total = base + incl;
-            team::sync();
-            const int32_t end = l.total;
-            constexpr int U = 4;  // products in flight per thread
-            for (int32_t q0 = base + t; q0 < end; q0 += U * T) {
-                int32_t q[U], w[U], c[U];
-                float b[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    q[u] = q0 + u * T < end ? q0 + u * T : end - 1;
-                    w[u] = 0;
-                }
-#pragma unroll
-                for (int s = T / 2; s > 0; s >>= 1) {  // the last entry that starts at or before q
-#pragma unroll
-                    for (int u = 0; u < U; ++u) w[u] += l.start[w[u] + s] <= q[u] ? s : 0;
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int32_t f = l.from[w[u]] + q[u];
-                    c[u] = g.b_ci[f];
-                    if constexpr (COMPUTE) b[u] = g.b_val[f];
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (q0 + u * T < end) {
-                        l.key[q[u]] = static_cast<K>(c[u]) << BITS | static_cast<uint32_t>(q[u]);
-                        if constexpr (COMPUTE) l.val[q[u]] = l.a[w[u]] * b[u];
-                    }
-                }
-            }
-            base = end;
-            team::sync();
-        }
+        each_product<COMPUTE>(g, l.deal, a0, a1, [&](uint32_t q, int32_t c, float v) {
+            l.key[q] = static_cast<K>(c) << BITS | q;
+            if constexpr (COMPUTE) l.val[q] = v;
+        });
         const int32_t out0 = COMPUTE ? g.c_ro[i] : 0;
         int32_t upto;  // the smallest network that holds the products
         if constexpr (T == kWave) {
@@ -641,8 +669,8 @@ __global__ __launch_bounds__(256) void gemm_clear_slots(gemm_args g, int64_t slo
         for (int64_t q : grid_stride_range(0, used * g.n)) g.slot_acc[q] = 0.f;
 }
 
-// A block per slot; a block past the rows leaves, so the slots that the queue's
-// rows use are the first ones.
+// More than kBitCols columns.  A block per slot; a block past the rows leaves, so
+// the slots that the queue's rows use are the first ones.
 template <bool COMPUTE>
 __global__ __launch_bounds__(kBlock) void gemm_tier3(gemm_args g) {
     using sched = group_mapped_scan<kBlock, indexed_tile_set>;
@@ -723,6 +751,96 @@ __global__ __launch_bounds__(kBlock) void gemm_tier3(gemm_args g) {
             if (tid == kBlock - 1) g.c_ro[i] = incl;
         }
         __threadfence();
+        __syncthreads();
+    }
+}
+
+// Up to kBitCols columns: the row's bitmap is in LDS (dynamic, a multiple of
+// kBitChunk columns), and counting never leaves it.  The compute pass enumerates
+// the products once for the bitmap, turns it into the place of every 16 columns'
+// first entry, writes the columns, and sums by place: kBitSums entries of C at a
+// time in LDS, the products enumerated again for each (a pass costs 3.6 ps a
+// product over the device, a global float atomic 48).  A row of more than
+// kBitPasses times that adds into the block's slot instead: one long row alone is
+// bound by its own block's passes.  kBitCols: the bitmap and the places take 64
+// KB, beside 64 KB of sums.  50,378 power-law rows squared: 143 us to compute and 31 to
+// count, against 627 and 281 with bitmap and sums in the slot.
+template <bool COMPUTE>
+__global__ __launch_bounds__(kBitBlock) void gemm_tier3_bits(gemm_args g) {
+    constexpr int T = kBitBlock;
+    extern __shared__ uint32_t s_bits[];  // the bitmap; compute: the place of each 16 columns in their chunk (16 bits)
+    __shared__ row_deal<T, kBlock, COMPUTE> s_deal;
+    __shared__ float s_sum[COMPUTE ? kBitSums : 1];
+    __shared__ int32_t s_place[COMPUTE ? kBitCols / kBitChunk : 1];  // first entry of a chunk
+    __shared__ int32_t s_slot;
+    static_assert(kBitSums * 4 >= kBitChunk * 2, "a chunk's columns are listed in the sums");
+    const int t = threadIdx.x;
+    if (static_cast<int32_t>(blockIdx.x) >= g.list_len[2]) return;  // uniform
+    const int32_t chunks = (g.n + kBitChunk - 1) / kBitChunk;
+    const int32_t words = chunks * (kBitChunk / 32);
+    for (int32_t w = t; w < words; w += T) s_bits[w] = 0u;
+    __syncthreads();
+    const queue_rounds rows{g.list_len + 3, &s_slot, 1, g.list_len[2]};
+    for (int64_t r : rows) {  // uniform across the block
+        const int32_t i = g.lists[2 * static_cast<int64_t>(g.m) + r];
+        const int32_t a0 = g.a_ro[i], a1 = g.a_ro[i + 1];
+        each_product<false>(g, s_deal, a0, a1,
+                            [&](uint32_t, int32_t c, float) { atomicOr(s_bits + (c >> 5), 1u << (c & 31)); });
+        if constexpr (COMPUTE) {
+            const uint16_t *half = reinterpret_cast<uint16_t *>(s_bits);  // 16 columns per thread and chunk
+            uint16_t *place = reinterpret_cast<uint16_t *>(s_bits + words);
+            uint16_t *list = reinterpret_cast<uint16_t *>(s_sum);
+            const int32_t out0 = g.c_ro[i];
+            int32_t out = 0;
+            for (int32_t k = 0; k < chunks; ++k) {  // uniform across the block
+                uint32_t m = half[k * T + t];
+                const int32_t cnt = __popc(m);
+                const int32_t incl = block_scan_incl<T>(cnt, s_deal.wave);
+                place[k * T + t] = static_cast<uint16_t>(incl - cnt);  // below kBitChunk where m != 0
+                if (t == T - 1) s_deal.total = incl, s_place[k] = out;
+                for (int32_t at = incl - cnt; m; m &= m - 1)
+                    list[at++] = static_cast<uint16_t>(t * 16 + __ffs(static_cast<int>(m)) - 1);
+                __syncthreads();
+                const int32_t total = s_deal.total;
+                for (int32_t q = t; q < total; q += T) g.c_ci[out0 + out + q] = k * kBitChunk + list[q];
+                out += total;
+                __syncthreads();
+            }
+            if (out <= kBitPasses * kBitSums) {
+                for (int32_t p0 = 0; p0 < out; p0 += kBitSums) {
+                    const int32_t here = out - p0 < kBitSums ? out - p0 : kBitSums;
+                    for (int32_t q = t; q < here; q += T) s_sum[q] = 0.f;
+                    __syncthreads();
+                    each_product<true>(g, s_deal, a0, a1, [&](uint32_t, int32_t c, float v) {
+                        const int32_t at = s_place[c / kBitChunk] + place[c >> 4] +
+                                           __popc(half[c >> 4] & ((1u << (c & 15)) - 1)) - p0;
+                        if (at >= 0 && at < here) unsafeAtomicAdd(s_sum + at, v);
+                    });
+                    for (int32_t q = t; q < here; q += T) g.c_val[out0 + p0 + q] = s_sum[q];
+                    __syncthreads();
+                }
+            } else {
+                float *acc = g.slot_acc + static_cast<int64_t>(blockIdx.x) * g.n;
+                each_product<true>(g, s_deal, a0, a1, [&](uint32_t, int32_t c, float v) { unsafeAtomicAdd(acc + c, v); });
+                __threadfence();
+                __syncthreads();
+                for (int32_t q = t; q < out; q += T) {
+                    const int32_t c = g.c_ci[out0 + q];
+                    g.c_val[out0 + q] = acc[c];
+                    acc[c] = 0.f;
+                }
+                __threadfence();  // the slot is clear before the next row adds to it
+            }
+            for (int32_t w = t; w < words; w += T) s_bits[w] = 0u;
+        } else {
+            int32_t cnt = 0;
+            for (int32_t w = t; w < words; w += T) {
+                cnt += __popc(s_bits[w]);
+                s_bits[w] = 0u;
+            }
+            const int32_t incl = block_scan_incl<T>(cnt, s_deal.wave);
+            if (t == T - 1) g.c_ro[i] = incl;
+        }
         __syncthreads();
     }
 }
@@ -872,9 +990,11 @@ static hipError_t gemm_pass(const spgemm_dev &P, int32_t *c_ro, int32_t *c_ci, f
         if (e != hipSuccess) return e;
     }
     const int64_t slots = spgemm_slots(P.n);
-    if (compute)
+    const bool bits_in_lds = P.n <= kBitCols;
+    // slots hold the rows of too many entries for LDS, and the bitmaps past kBitCols
+    if (compute && P.n > kBitPasses * kBitSums)
         hipLaunchKernelGGL(gemm_clear_slots<true>, dim3(1024), dim3(256), 0, s, g, slots);
-    else
+    else if (!bits_in_lds)
         hipLaunchKernelGGL(gemm_clear_slots<false>, dim3(256), dim3(256), 0, s, g, slots);
     // one launch per tier (each reads its list's length on the device)
     const uint32_t grid12 = static_cast<uint32_t>(capped(P.m, 1) < 2048 ? capped(P.m, 1) : 2048);
@@ -898,7 +1018,12 @@ static hipError_t gemm_pass(const spgemm_dev &P, int32_t *c_ro, int32_t *c_ci, f
     }
     {
         prof_scope p(s, names[c][3]);
-        if (compute)
+        const size_t bitmap = static_cast<size_t>((P.n + kBitChunk - 1) / kBitChunk) * (kBitChunk / 8);
+        if (bits_in_lds && compute)
+            hipLaunchKernelGGL(gemm_tier3_bits<true>, dim3(static_cast<uint32_t>(slots)), dim3(kBitBlock), 2 * bitmap, s, g);
+        else if (bits_in_lds)
+            hipLaunchKernelGGL(gemm_tier3_bits<false>, dim3(static_cast<uint32_t>(slots)), dim3(kBitBlock), bitmap, s, g);
+        else if (compute)
             hipLaunchKernelGGL(gemm_tier3<true>, dim3(static_cast<uint32_t>(slots)), dim3(kBlock), 0, s, g);
         else
             hipLaunchKernelGGL(gemm_tier3<false>, dim3(static_cast<uint32_t>(slots)), dim3(kBlock), 0, s, g);
