@@ -22,7 +22,8 @@
 //
 // An iteration is one launch, persistent (the resident grid), that reads the
 // frontier size from device memory, so the host enqueues a batch of
-// iterations without waiting and reads the size once per batch to stop.
+// iterations without waiting and reads the size once per batch to stop.  (The
+// merge-path advance may take several small frontiers in one launch.)
 // Three rotating counters: launch i reads counter i % 3, appends to
 // (i + 1) % 3 and zeroes (i + 2) % 3, the one launch i + 1 appends to (and
 // launch i - 1 last read), so no memset and no host round trip is needed.
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(group_block<G>::BLOCK) void advance_scan_kernel(tra
 
 // ---------------------------------------------------------------- merge-path over the frontier
 //
-// One launch per iteration.  The frontier carries its own "row offsets": the
+// One launch per iteration, or several small ones.  The frontier carries its own "row offsets": the
 // vertices that have out-edges are stored in slots with the exclusive prefix sum
 // of their degrees, because a block reserves its new vertices' slots and edges
 // with one 64-bit atomicAdd (slots in the low word, edges in the high one), so
@@ -241,7 +242,7 @@ __global__ __launch_bounds__(group_block<G>::BLOCK) void advance_scan_kernel(tra
 // waited for three dependent loads each.  The earlier form's four launches per
 // iteration for the offsets (degree scan in three, split) are gone.  1M-vertex
 // power-law graph, 30.8M edges: BFS 576 -> 365 us, SSSP 2.48 -> 1.55 ms; a
-// 200 x 200 grid, BFS in 335 iterations, 7.2 -> 3.4 ms.  512 x 4 edges: 256 x 8
+// 200 x 200 grid, BFS in 335 iterations, 7.2 -> 3.4 ms (with kSmallIters 1.66).  512 x 4 edges: 256 x 8
 // has fewer wavefronts for the LDS a unit takes (396 us, 1.64 ms), 1024 x 2 fewer
 // blocks (504 us, 1.86 ms).  Bound: the random target states (24M in 180 us) and
 // returning atomics, both device-wide.
@@ -262,7 +263,16 @@ struct edge_args {
     int32_t *off_out;
     const unsigned long long *pk_in;  // slots | edges << 32 of the frontier
     unsigned long long *pk_out, *pk_clear;
+    const int32_t *done_in;  // iterations before this launch
+    int32_t *done_out;
+    int32_t max_iter;
 };
+
+// A frontier of one unit of edges or less is the work of one block, which goes on
+// with the next one itself, up to this many iterations a launch: it knows the next
+// frontier's size, and a launch, its gap and its start cost more than the unit
+// (MEASURED4).
+constexpr int32_t kSmallIters = 256;
 
 // Inclusive prefix sum over the block of a 64-bit value; s_wave holds BLOCK/64.
 template <int BLOCK>
@@ -289,30 +299,40 @@ __global__ __launch_bounds__(kEdgeBlock) void advance_merge_kernel(trav_args t, 
     __shared__ float s_du[BFS ? 1 : kEdgeSlots];
     __shared__ int32_t s_new[kEdgeNew];  // vertices for the next frontier
     __shared__ unsigned long long s_wave[kEdgeBlock / kWave];
-    __shared__ unsigned long long s_got;
+    __shared__ unsigned long long s_got, s_next;
     __shared__ int32_t s_iwave[kEdgeBlock / kWave];
     __shared__ int32_t s_pair, s_held;
     const int tid = threadIdx.x;
     const bool live = *t.cnt_in != 0;
     const unsigned long long pk = *x.pk_in;
+    int32_t iter = *x.done_in;
+    const bool stop = iter >= x.max_iter;  // the frontier is left as it is
+    int32_t nf = static_cast<int32_t>(pk & 0xffffffffu), E = static_cast<int32_t>(pk >> 32);
+    const int32_t units = stop ? 0 : E / kEdgeUnit + (E % kEdgeUnit != 0);
+    const bool single = units == 1;  // the last block's, which publishes the next frontier
     if (blockIdx.x == 0 && tid == 0) {
         *t.cnt_clear = 0;
         *x.pk_clear = 0;
-        if (live) *t.rounds += 1;
+        if (!single) *x.done_out = iter + (live && !stop);
+        if (stop) *t.cnt_out = live;
     }
-    const int32_t nf = static_cast<int32_t>(pk & 0xffffffffu), E = static_cast<int32_t>(pk >> 32);
-    const int32_t npairs = (nf + 1) / 2;
-    const int32_t units = (E + kEdgeUnit - 1) / kEdgeUnit;
     // contiguous ranges of units: block b takes [b * units / grid, (b + 1) * units / grid)
     const int32_t u0 = static_cast<int32_t>(static_cast<int64_t>(blockIdx.x) * units / gridDim.x);
     const int32_t u1 = static_cast<int32_t>(static_cast<int64_t>(blockIdx.x + 1) * units / gridDim.x);
     if (u0 >= u1) return;  // uniform
-    if (wave_id() == 0) {  // the last pair that starts at or before the range's first edge
+    if (single) {
+        if (tid == 0) s_pair = 0;
+    } else if (wave_id() == 0) {  // the last pair that starts at or before the range's first edge
         const int32_t *off = x.off_in;
-        const int32_t c = group_count_below<kWave>(0, npairs, u0 * kEdgeUnit + 1, [off](int32_t q) { return off[q]; });
+        const int32_t c = group_count_below<kWave>(0, (nf + 1) / 2, u0 * kEdgeUnit + 1, [off](int32_t q) { return off[q]; });
         if (lane_id() == 0) s_pair = c - 1;
     }
     __syncthreads();
+    int32_t small = 0;  // iterations of this launch, by one block
+    auto goes_on = [&](unsigned long long next) {
+        const uint32_t edges = static_cast<uint32_t>(next >> 32);
+        return edges > 0 && edges <= kEdgeUnit && small + 1 < kSmallIters && iter + 1 < x.max_iter;
+    };
     // Slots and edges for the n vertices held, a contiguous share per thread.
     auto flush_new = [&](int32_t n) {  // every thread of the block
         if (n == 0) return;
@@ -332,130 +352,168 @@ __global__ __launch_bounds__(kEdgeBlock) void advance_merge_kernel(trav_args t, 
             if (deg[i] > 0) mine += (static_cast<unsigned long long>(deg[i]) << 32) | 1u;
         const unsigned long long incl = block_scan_incl64<kEdgeBlock>(mine, s_wave);
         if (tid == kEdgeBlock - 1) {
-            s_got = incl ? atomicAdd(x.pk_out, incl) : 0;
-            *t.cnt_out = 1;
+            s_next = incl;
+            s_got = 0;
+            if (!single) {
+                if (incl) s_got = atomicAdd(x.pk_out, incl);
+                *t.cnt_out = 1;
+            }
         }
         __syncthreads();
         unsigned long long at = s_got + (incl - mine);
+        if (single && goes_on(s_next)) {  // uniform: staged for this block's next iteration
 #pragma unroll
-        for (int i = 0; i < S; ++i) {
-            if (deg[i] > 0) {
-                const uint32_t pos = static_cast<uint32_t>(at);
-                t.q_out[pos] = v[i];
-                if ((pos & 1) == 0) x.off_out[pos >> 1] = static_cast<int32_t>(at >> 32);
-                at += (static_cast<unsigned long long>(deg[i]) << 32) | 1u;
+            for (int i = 0; i < S; ++i) {
+                if (deg[i] > 0) {
+                    const uint32_t pos = static_cast<uint32_t>(at);
+                    const int32_t off = static_cast<int32_t>(at >> 32);
+                    s_off[pos] = off;
+                    s_base[pos] = t.ro[v[i]] - off;
+                    // the atomics' value: a line of this CU's L1 may be older
+                    if constexpr (!BFS)
+                        s_du[pos] = __hip_atomic_load(t.dist + v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    at += (static_cast<unsigned long long>(deg[i]) << 32) | 1u;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < S; ++i) {
+                if (deg[i] > 0) {
+                    const uint32_t pos = static_cast<uint32_t>(at);
+                    t.q_out[pos] = v[i];
+                    if ((pos & 1) == 0) x.off_out[pos >> 1] = static_cast<int32_t>(at >> 32);
+                    at += (static_cast<unsigned long long>(deg[i]) << 32) | 1u;
+                }
             }
         }
         __syncthreads();
     };
-    int32_t held = 0;
-    for (int32_t u = u0; u < u1; ++u) {  // uniform across the block
-        const int32_t e0 = u * kEdgeUnit;
-        const int32_t e1 = E - e0 < kEdgeUnit ? E : e0 + kEdgeUnit;
-        const int32_t p0 = s_pair;
-        int32_t slots = 0;  // staged, of pairs that begin in the unit or before it
-        for (int32_t b = 0;; b += kEdgeBlock) {  // uniform
-            const int32_t q = p0 + b + tid, at = 2 * (b + tid);
-            int32_t o0 = INT32_MAX, o1 = INT32_MAX;
-            if (q < npairs) {
-                o0 = x.off_in[q];
-                if (o0 < e1) {
-                    const bool two = 2 * q + 1 < nf;
-                    const int32_t v0 = t.q_in[2 * q], v1 = t.q_in[two ? 2 * q + 1 : 2 * q];
-                    const int32_t f0 = t.ro[v0], l0 = t.ro[v0 + 1], f1 = t.ro[v1];
-                    if (two) o1 = o0 + (l0 - f0);
-                    s_base[at] = f0 - o0;
-                    s_base[at + 1] = f1 - o1;
-                    if constexpr (!BFS) {
-                        s_du[at] = t.dist[v0];
-                        s_du[at + 1] = t.dist[v1];
+    for (;; ++small) {  // uniform across the block
+        int32_t held = 0, fresh = 0;
+        for (int32_t u = u0; u < u1; ++u) {  // uniform across the block
+            const int32_t e0 = u * kEdgeUnit;
+            const int32_t n = E - e0 < kEdgeUnit ? E - e0 : kEdgeUnit;  // its edges
+            const int32_t e1 = e0 + n, npairs = (nf + 1) / 2;
+            const int32_t p0 = s_pair;
+            int32_t slots = small ? nf : 0;  // staged: by the iteration before, or of pairs that begin in the unit or before it
+            for (int32_t b = 0; small == 0; b += kEdgeBlock) {  // uniform
+                const int32_t q = p0 + b + tid, at = 2 * (b + tid);
+                int32_t o0 = INT32_MAX, o1 = INT32_MAX;
+                if (q < npairs) {
+                    o0 = x.off_in[q];
+                    if (o0 < e1) {
+                        const bool two = 2 * q + 1 < nf;
+                        const int32_t v0 = t.q_in[2 * q], v1 = t.q_in[two ? 2 * q + 1 : 2 * q];
+                        const int32_t f0 = t.ro[v0], l0 = t.ro[v0 + 1], f1 = t.ro[v1];
+                        if (two) o1 = o0 + (l0 - f0);
+                        s_base[at] = f0 - o0;
+                        s_base[at + 1] = f1 - o1;
+                        if constexpr (!BFS) {
+                            s_du[at] = t.dist[v0];
+                            s_du[at + 1] = t.dist[v1];
+                        }
                     }
                 }
+                s_off[at] = o0;
+                s_off[at + 1] = o1;
+                const int32_t pairs = __syncthreads_count(o0 < e1);
+                slots += 2 * pairs;
+                if (pairs < kEdgeBlock) break;
             }
-            s_off[at] = o0;
-            s_off[at + 1] = o1;
-            const int32_t pairs = __syncthreads_count(o0 < e1);
-            slots += 2 * pairs;
-            if (pairs < kEdgeBlock) break;
-        }
-        // each edge's slot: the last with s_off <= e
-        int32_t slot[kEdgeItems];
+            // each edge's slot: the last with s_off <= e
+            int32_t slot[kEdgeItems];
 #pragma unroll
-        for (int i = 0; i < kEdgeItems; ++i) slot[i] = 0;
-        int32_t step = 1;
-        while (step < slots) step <<= 1;
-        for (step >>= 1; step > 0; step >>= 1) {  // uniform
+            for (int i = 0; i < kEdgeItems; ++i) slot[i] = 0;
+            int32_t step = 1;
+            while (step < slots) step <<= 1;
+            for (step >>= 1; step > 0; step >>= 1) {  // uniform
+#pragma unroll
+                for (int i = 0; i < kEdgeItems; ++i) {
+                    const int32_t at = slot[i] + step;
+                    if (at < slots && s_off[at < slots ? at : 0] - e0 <= tid + i * kEdgeBlock) slot[i] = at;
+                }
+            }
+            int32_t v[kEdgeItems];
+            float offer[kEdgeItems];
+            bool want[kEdgeItems];
 #pragma unroll
             for (int i = 0; i < kEdgeItems; ++i) {
-                const int32_t at = slot[i] + step;
-                if (at < slots && s_off[at < slots ? at : 0] <= e0 + tid + i * kEdgeBlock) slot[i] = at;
+                const int32_t e = tid + i * kEdgeBlock;
+                want[i] = e < n;
+                v[i] = 0;
+                offer[i] = 0.f;
+                if (want[i]) {
+                    const int32_t g = s_base[slot[i]] + e0 + e;
+                    v[i] = ld_stream(t.ci + g);
+                    if constexpr (!BFS) offer[i] = ld_stream(t.w + g);
+                }
+                if (e == n - 1) s_pair = p0 + slot[i] / 2;  // the next unit begins in this pair or after it
             }
-        }
-        int32_t v[kEdgeItems];
-        float offer[kEdgeItems];
-        bool want[kEdgeItems];
+            // the target's state, which only falls (SSSP) or is claimed once (BFS): a
+            // stale read lets an offer through to the atomic, which decides
+            if constexpr (BFS) {
+                int32_t seen[kEdgeItems];
 #pragma unroll
-        for (int i = 0; i < kEdgeItems; ++i) {
-            const int32_t e = e0 + tid + i * kEdgeBlock;
-            want[i] = e < e1;
-            v[i] = 0;
-            offer[i] = 0.f;
-            if (want[i]) {
-                const int32_t g = s_base[slot[i]] + e;
-                v[i] = ld_stream(t.ci + g);
-                if constexpr (!BFS) offer[i] = ld_stream(t.w + g);
+                for (int i = 0; i < kEdgeItems; ++i) seen[i] = want[i] ? t.depth[v[i]] : 0;
+#pragma unroll
+                for (int i = 0; i < kEdgeItems; ++i)
+                    if (want[i] && seen[i] == kUnvisited) seen[i] = atomicCAS(t.depth + v[i], kUnvisited, iter + 1);
+#pragma unroll
+                for (int i = 0; i < kEdgeItems; ++i) want[i] = want[i] && seen[i] == kUnvisited;
+            } else {
+                float seen[kEdgeItems];
+#pragma unroll
+                for (int i = 0; i < kEdgeItems; ++i) {
+                    offer[i] = s_du[slot[i]] + offer[i];
+                    seen[i] = want[i] ? t.dist[v[i]] : 0.f;
+                }
+#pragma unroll
+                for (int i = 0; i < kEdgeItems; ++i) {
+                    want[i] = want[i] && offer[i] < seen[i];
+                    if (want[i])
+                        seen[i] = __int_as_float(
+                            atomicMin(reinterpret_cast<int32_t *>(t.dist) + v[i], __float_as_int(offer[i])));
+                }
+                int32_t last[kEdgeItems];
+#pragma unroll
+                for (int i = 0; i < kEdgeItems; ++i) {
+                    want[i] = want[i] && offer[i] < seen[i];
+                    last[i] = want[i] ? atomicExch(t.stamp + v[i], iter) : 0;
+                }
+#pragma unroll
+                for (int i = 0; i < kEdgeItems; ++i) want[i] = want[i] && last[i] != iter;
             }
-            if (e == e1 - 1) s_pair = p0 + slot[i] / 2;  // the next unit begins in this pair or after it
-        }
-        // the target's state, which only falls (SSSP) or is claimed once (BFS): a
-        // stale read lets an offer through to the atomic, which decides
-        if constexpr (BFS) {
-            int32_t seen[kEdgeItems];
+            // the unit's new vertices join the block's
+            int32_t mine = 0;
 #pragma unroll
-            for (int i = 0; i < kEdgeItems; ++i) seen[i] = want[i] ? t.depth[v[i]] : 0;
+            for (int i = 0; i < kEdgeItems; ++i) mine += want[i] ? 1 : 0;
+            const int32_t incl = block_scan_incl<kEdgeBlock>(mine, s_iwave);
+            int32_t at = held + incl - mine;
 #pragma unroll
             for (int i = 0; i < kEdgeItems; ++i)
-                if (want[i] && seen[i] == kUnvisited) seen[i] = atomicCAS(t.depth + v[i], kUnvisited, t.iter + 1);
-#pragma unroll
-            for (int i = 0; i < kEdgeItems; ++i) want[i] = want[i] && seen[i] == kUnvisited;
-        } else {
-            float seen[kEdgeItems];
-#pragma unroll
-            for (int i = 0; i < kEdgeItems; ++i) {
-                offer[i] = s_du[slot[i]] + offer[i];
-                seen[i] = want[i] ? t.dist[v[i]] : 0.f;
+                if (want[i]) s_new[at++] = v[i];
+            if (tid == kEdgeBlock - 1) s_held = held + incl;
+            __syncthreads();
+            held = s_held;  // (the next unit's scan orders this read before the next write)
+            fresh = held;
+            if (held > kEdgeNew - kEdgeUnit || u + 1 == u1) {  // uniform
+                flush_new(held);
+                held = 0;
             }
-#pragma unroll
-            for (int i = 0; i < kEdgeItems; ++i) {
-                want[i] = want[i] && offer[i] < seen[i];
-                if (want[i])
-                    seen[i] = __int_as_float(
-                        atomicMin(reinterpret_cast<int32_t *>(t.dist) + v[i], __float_as_int(offer[i])));
-            }
-            int32_t last[kEdgeItems];
-#pragma unroll
-            for (int i = 0; i < kEdgeItems; ++i) {
-                want[i] = want[i] && offer[i] < seen[i];
-                last[i] = want[i] ? atomicExch(t.stamp + v[i], t.iter) : 0;
-            }
-#pragma unroll
-            for (int i = 0; i < kEdgeItems; ++i) want[i] = want[i] && last[i] != t.iter;
         }
-        // the unit's new vertices join the block's
-        int32_t mine = 0;
-#pragma unroll
-        for (int i = 0; i < kEdgeItems; ++i) mine += want[i] ? 1 : 0;
-        const int32_t incl = block_scan_incl<kEdgeBlock>(mine, s_iwave);
-        int32_t at = held + incl - mine;
-#pragma unroll
-        for (int i = 0; i < kEdgeItems; ++i)
-            if (want[i]) s_new[at++] = v[i];
-        if (tid == kEdgeBlock - 1) s_held = held + incl;
-        __syncthreads();
-        held = s_held;  // (the next unit's scan orders this read before the next write)
-        if (held > kEdgeNew - kEdgeUnit || u + 1 == u1) {  // uniform
-            flush_new(held);
-            held = 0;
+        if (!single) return;
+        const unsigned long long next = fresh ? s_next : 0;
+        nf = static_cast<int32_t>(next & 0xffffffffu);
+        E = static_cast<int32_t>(next >> 32);
+        const bool on = goes_on(next);
+        ++iter;
+        if (!on) {
+            if (tid == 0) {
+                *x.pk_out = next;
+                *t.cnt_out = fresh != 0;
+                *x.done_out = iter;
+            }
+            return;
         }
     }
 }
@@ -464,7 +522,7 @@ template <bool BFS>
 __global__ __launch_bounds__(256) void traversal_init_kernel(int32_t n, int32_t source, float *dist,
                                                              int32_t *depth, int32_t *stamp, int32_t *q0,
                                                              int32_t *counters, const int32_t *ro, int32_t *off0,
-                                                             unsigned long long *pk) {
+                                                             unsigned long long *pk, int32_t *done) {
     for (int64_t v : grid_stride_range(0, n)) {
         if constexpr (BFS) {
             depth[v] = v == source ? 0 : kUnvisited;
@@ -486,6 +544,7 @@ __global__ __launch_bounds__(256) void traversal_init_kernel(int32_t n, int32_t 
         off0[0] = 0;
         pk[0] = d > 0 ? (static_cast<unsigned long long>(d) << 32) | 1u : 0u;
         pk[1] = pk[2] = 0;
+        done[0] = 0;
     }
 }
 
@@ -507,17 +566,18 @@ hipError_t launch_advance(K kernel, int block, int grid, const trav_args &t, hip
 }
 
 template <bool BFS>
-hipError_t advance_merge(const trav_cfg &c, const trav_ws &w, const trav_args &t, hipStream_t s) {
+hipError_t advance_merge(const trav_cfg &c, const trav_ws &w, const trav_args &t, int32_t max_iter, hipStream_t s) {
     const int32_t i = t.iter;
-    const edge_args x{w.off[i & 1], w.off[(i + 1) & 1], w.pk + i % 3, w.pk + (i + 1) % 3, w.pk + (i + 2) % 3};
+    const edge_args x{w.off[i & 1], w.off[(i + 1) & 1], w.pk + i % 3, w.pk + (i + 1) % 3, w.pk + (i + 2) % 3,
+                      w.done + i % 3, w.done + (i + 1) % 3, max_iter};
     hipLaunchKernelGGL(advance_merge_kernel<BFS>, dim3(static_cast<uint32_t>(c.grid)), dim3(kEdgeBlock), 0, s, t, x);
     return hipGetLastError();
 }
 
 template <bool BFS>
-hipError_t advance(const trav_cfg &c, const trav_ws &w, const trav_args &t, hipStream_t s) {
+hipError_t advance(const trav_cfg &c, const trav_ws &w, const trav_args &t, int32_t max_iter, hipStream_t s) {
     prof_scope p(s, BFS ? "bfs_advance" : "sssp_advance");
-    if (c.kind == LB_MERGE_PATH) return advance_merge<BFS>(c, w, t, s);
+    if (c.kind == LB_MERGE_PATH) return advance_merge<BFS>(c, w, t, max_iter, s);
     if (c.kind == LB_THREAD_MAPPED) return launch_advance(advance_thread_kernel<BFS>, c.block, c.grid, t, s);
 #define LB_G(G)                                                                                               \
     if (c.group == G) {                                                                                       \
@@ -540,7 +600,8 @@ hipError_t run_traversal(const csr_dev &G, int32_t source, float *dist, int32_t 
         prof_scope p(s, "traversal_init");
         const int64_t blocks = (static_cast<int64_t>(G.rows) + 255) / 256;
         hipLaunchKernelGGL(traversal_init_kernel<BFS>, dim3(static_cast<uint32_t>(blocks < 8192 ? blocks : 8192)),
-                           dim3(256), 0, s, G.rows, source, dist, depth, w.stamp, w.queue[0], w.counters, G.ro, w.off[0], w.pk);
+                           dim3(256), 0, s, G.rows, source, dist, depth, w.stamp, w.queue[0], w.counters, G.ro, w.off[0], w.pk,
+                           w.done);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -551,7 +612,7 @@ hipError_t run_traversal(const csr_dev &G, int32_t source, float *dist, int32_t 
     // launched 28 iterations for 13); a long chain or grid pays for each wait.
     int32_t launched = 0;
     if (c.kind == LB_MERGE_PATH && c.grid <= 0) c.grid = resident_blocks(advance_merge_kernel<BFS>, kEdgeBlock);
-    int32_t host[4] = {0, 0, 0, 0};
+    int32_t host[kTravDone + 3] = {}, rounds = 0;
     *converged = false;
     for (;;) {
         const int32_t batch = launched < 16 ? 4 : (launched < 32 ? launched : 32);
@@ -564,19 +625,20 @@ hipError_t run_traversal(const csr_dev &G, int32_t source, float *dist, int32_t 
             t.cnt_clear = w.counters + (launched + 2) % 3;
             t.ticket = w.counters + 4 + (launched & 1);
             t.ticket_clear = w.counters + 4 + ((launched + 1) & 1);
-            const hipError_t e = advance<BFS>(c, w, t, s);
+            const hipError_t e = advance<BFS>(c, w, t, max_iter, s);
             if (e != hipSuccess) return e;
         }
         hipError_t e = hipMemcpyAsync(host, w.counters, sizeof host, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return e;
+        rounds = c.kind == LB_MERGE_PATH ? host[kTravDone + launched % 3] : host[3];
         if (host[launched % 3] == 0) {
             *converged = true;
             break;
         }
-        if (launched >= max_iter) break;
+        if (rounds >= max_iter || launched >= max_iter) break;  // a launch is at least one iteration
     }
-    if (iterations) *iterations = host[3];
+    if (iterations) *iterations = rounds;
     return hipSuccess;
 }
 

@@ -352,7 +352,7 @@ struct trav_cfg {
 // Workspace: stamp[n], two frontier queues of n vertex ids, counters (three
 // rotating frontier sizes, the count of non-empty frontiers, two rotating
 // work-queue tickets; at byte 64, three rotating 64-bit {slots, edges} of the
-// merge-path frontier), and the merge-path frontiers' offsets of even slots
+// merge-path frontier, at byte 96 three rotating counts of its iterations), and the merge-path frontiers' offsets of even slots
 // (2 ceil(n / 2) <= n + 1).  The size also covers a split at every 2048 merge
 // items, which nothing uses any more: callers may keep workspaces by size.
 struct trav_ws {
@@ -361,7 +361,9 @@ struct trav_ws {
     int32_t *counters;
     int32_t *off[2];
     unsigned long long *pk;
+    int32_t *done;
 };
+constexpr int kTravDone = 24;  // `done` among the counters
 inline size_t trav_ws_bytes(int64_t n, int64_t nnz) {
     const size_t q = align256(static_cast<size_t>(n) * 4);
     const size_t units = static_cast<size_t>((n + nnz + 2047) / 2048) + 1;
@@ -377,6 +379,7 @@ inline trav_ws trav_ws_carve(void *base, int64_t n) {
     w.queue[1] = reinterpret_cast<int32_t *>(p + 2 * q);
     w.counters = reinterpret_cast<int32_t *>(p + 3 * q);
     w.pk = reinterpret_cast<unsigned long long *>(p + 3 * q + 64);
+    w.done = w.counters + kTravDone;
     w.off[0] = reinterpret_cast<int32_t *>(p + 3 * q + 256);
     w.off[1] = w.off[0] + (n + 1) / 2;
     return w;
