@@ -371,7 +371,10 @@ LB_API lb_status_t lb_spmm(const lb_csr_t *A, const void *X, lb_dtype_t x_dtype,
  * dvalues[j] = dy[row(j)] * x[col_idx[j]] (nnz float32, a single rounding
  * of the exact product).  Either output may be NULL to skip it.  x is read
  * only for dvalues.  Runs over the merge-path split of A (s->kind must be
- * LB_MERGE_PATH or LB_AUTO); workspace from lb_workspace_size(A, s, 0). */
+ * LB_MERGE_PATH or LB_AUTO); workspace from lb_workspace_size(A, s, 0), which
+ * for larger matrices holds the products of dx, sorted by target range (6
+ * bytes per nonzero); with the split's own size only, dx takes one float
+ * atomic per nonzero. */
 LB_API lb_status_t lb_spmv_backward(const lb_csr_t *A, const void *x, lb_dtype_t x_dtype,
                                     const float *dy, float *dx, float *dvalues,
                                     const lb_schedule_t *s, void *workspace,
@@ -385,12 +388,14 @@ LB_API lb_status_t lb_spmv_backward(const lb_csr_t *A, const void *x, lb_dtype_t
  * increasing row of A), the same for every build; it is computed by a
  * stable radix sort of the entries by column (digits of at most 7 bits:
  * three passes for cols <= 2^21), with block-local histograms, tiles
- * sorted in LDS and written as runs, and no global atomics.  Workspace from lb_transpose_workspace_size (24 bytes per
- * nonzero plus the histograms).  cols + nnz < 2^31 - 1.
+ * sorted in LDS and written as runs, and no global atomics.  Workspace from
+ * lb_transpose_workspace_size (24 bytes per nonzero plus the histograms).
+ * cols + nnz < 2^31 - 1.
  * lb_spmv_backward_transposed then computes dvalues as lb_spmv_backward
  * does (bit-exact) and dx = A^T dy by the merge-path SpMV on A^T, which
- * reads the current values of A through perm (a gather, no atomics, no
- * permuted copy); dx is bit-reproducible (the transpose is canonical).  s as for
+ * reads the current values of A, or for large matrices with dvalues the
+ * products values[j] * dy[row(j)] written beside them, through perm (a gather,
+ * no atomics); dx is bit-reproducible (the transpose is canonical).  s as for
  * lb_spmv_backward (merge-path block_size / items_per_thread); workspace
  * from lb_backward_transposed_workspace_size. */
 LB_API lb_status_t lb_transpose_workspace_size(const lb_csr_t *A, size_t *bytes);
@@ -508,10 +513,12 @@ LB_API lb_status_t lb_coo_merge_path_partition(const int32_t *row_idx, int64_t r
 /* CSC: y = A x with columns as tiles: entry j adds values[j] * x[c] into
  * y[row_idx[j]].  x is float32 (values float32 or BF16); y (rows float32,
  * coarse-grained device memory) is zeroed by the call and accumulated with
- * float atomics, so it is not bit-reproducible run to run.  Each block first sums its unit's products
- * per row in LDS, so a row hit from many columns costs one atomic per
- * block.  LB_MERGE_PATH or LB_AUTO (the merge-path split of the columns;
- * block_size/items_per_thread as for CSR, default 512 x 8 here: larger
+ * float atomics, so it is not bit-reproducible run to run.  Larger matrices go
+ * by row ranges, each summed in float64 in LDS, with units of their own;
+ * otherwise, and with a workspace of the split's size only, each block sums its
+ * unit's products per row in LDS, so a row hit from many columns costs one
+ * atomic per block.  LB_MERGE_PATH or LB_AUTO (the merge-path split of the
+ * columns; block_size/items_per_thread as for CSR, default 512 x 8 here: larger
  * units combine more).  cols + nnz < 2^31 - 1.  Workspace from
  * lb_csc_workspace_size. */
 LB_API lb_status_t lb_csc_workspace_size(const lb_csc_t *A, const lb_schedule_t *s, size_t *bytes);
@@ -526,10 +533,10 @@ LB_API lb_status_t lb_spmv_csc(const lb_csc_t *A, const void *x, lb_dtype_t x_dt
  * product A[i, j] * B[j, c], ascending (structural: kept even if the sum is
  * 0), with value sum_j A[i, j] * B[j, c] in float32.  Rows are accumulated
  * by product count: up to 32 products an 8-lane group, up to 256 one
- * wavefront, up to 4096 one block
- * (both sort (column, product index) in LDS and sum in product order:
- * deterministic), beyond that a dense slot per block of a work queue (float
- * atomics: summation order varies run to run).
+ * wavefront, up to 4096 one block (they sort (column, product index) in
+ * registers and sum in product order: deterministic), beyond that a block of a
+ * work queue (float atomics, in LDS up to 2^18 columns, else in a dense slot:
+ * summation order varies run to run).
  * lb_spgemm_count (synchronizing) writes C's row offsets (A->rows + 1,
  * device) and *c_nnz (host); the caller allocates col_idx and values of
  * *c_nnz entries; lb_spgemm_compute fills them.  Both take the workspace of
@@ -554,8 +561,8 @@ LB_API lb_status_t lb_spgemm_compute(const lb_csr_t *A, const lb_csr_t *B, const
  * Each iteration takes the current frontier (a device list of vertex ids:
  * an indexed tile set) and relaxes every out-edge of its vertices under the
  * schedule s; the vertices that improve form the next frontier, each listed
- * once.  The host launches again while the frontier holds vertices (Sec. 5.3), reading
- * the frontier size from the device once per batch of iterations, so these
+ * once.  The host launches again while the frontier holds vertices (Sec. 5.3; a
+ * merge-path launch may take several small frontiers), reading the frontier size from the device once per batch of iterations, so these
  * calls synchronize `stream`.
  * Schedules: LB_THREAD_MAPPED (a thread per frontier vertex, block_size as
  * for SpMV), LB_WORK_QUEUE (group_size in [8, 1024]: frontier chunks handed
