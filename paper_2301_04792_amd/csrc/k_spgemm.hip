@@ -72,8 +72,15 @@ __device__ __forceinline__ void wave_sync() {
 
 // ---------------------------------------------------------------- products per row and tiers
 
+// Both forms also zero the counters that the kernels after them append by, in
+// place of a fill launch of 3 us and its gap.
+__device__ __forceinline__ void clear_counters(const gemm_args &g) {
+    if (blockIdx.x == 0 && threadIdx.x < 5) g.list_len[threadIdx.x] = 0;
+}
+
 // A wavefront per row of A (rows of eight or more entries on average).
 __global__ __launch_bounds__(256) void gemm_products_rows(gemm_args g, int64_t *__restrict__ prod) {
+    clear_counters(g);
     const group_mapped<kWave, csr_tile_set> sch{{g.a_ro, g.m, 0}};
     for (int64_t i : sch.tiles()) {
         int64_t p = 0;
@@ -96,6 +103,7 @@ constexpr int kProdRows = 512;
 __global__ __launch_bounds__(256) void gemm_products(gemm_args g, int64_t *__restrict__ prod) {
     __shared__ int32_t s_end[kProdRows];
     __shared__ unsigned long long s_cnt[kProdRows];
+    clear_counters(g);
     const int tid = threadIdx.x;
     const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kProdRows;
     const int32_t rows = static_cast<int32_t>(g.m - r0 < kProdRows ? g.m - r0 : kProdRows);
@@ -970,8 +978,7 @@ static hipError_t gemm_pass(const spgemm_dev &P, int32_t *c_ro, int32_t *c_ci, f
     const gemm_ws w = gemm_carve(ws, P.m, P.n);
     gemm_args g{P.m, P.n, P.a_ro, P.a_ci, P.a_val, P.b_ro, P.b_ci, P.b_val, w.prod, w.lists, w.list_len,
                 c_ro, c_ci, c_val, w.slot_acc, w.slot_bits, w.slot_words};
-    hipError_t e = fill_f32(reinterpret_cast<float *>(w.list_len), 5, 0.f, s);  // +0.0f is all zero bits
-    if (e != hipSuccess) return e;
+    hipError_t e;
     {
         prof_scope p(s, "spgemm_products");
         // short rows (fewer than 8 entries on average) share wavefronts; longer ones get one each
@@ -981,8 +988,8 @@ static hipError_t gemm_pass(const spgemm_dev &P, int32_t *c_ro, int32_t *c_ci, f
         } else {
             constexpr int GPB = group_block<kWave>::GPB;  // grid-stride: at most 2^16 blocks
             const int64_t want = (static_cast<int64_t>(P.m) + GPB - 1) / GPB;
-            hipLaunchKernelGGL(gemm_products_rows, dim3(static_cast<uint32_t>(want < 65536 ? want : 65536)), dim3(256),
-                               0, s, g, w.prod);
+            const int64_t grid = want < 1 ? 1 : (want < 65536 ? want : 65536);
+            hipLaunchKernelGGL(gemm_products_rows, dim3(static_cast<uint32_t>(grid)), dim3(256), 0, s, g, w.prod);
         }
         const int64_t cb = (static_cast<int64_t>(P.m) + kClassRows - 1) / kClassRows;
         hipLaunchKernelGGL(gemm_classify, dim3(static_cast<uint32_t>(cb < 1 ? 1 : cb)), dim3(kClassBlock), 0, s, g);
