@@ -372,9 +372,11 @@ LB_API lb_status_t lb_spmm(const lb_csr_t *A, const void *X, lb_dtype_t x_dtype,
  * of the exact product).  Either output may be NULL to skip it.  x is read
  * only for dvalues.  Runs over the merge-path split of A (s->kind must be
  * LB_MERGE_PATH or LB_AUTO); workspace from lb_workspace_size(A, s, 0), which
- * for larger matrices holds the products of dx, sorted by target range (6
- * bytes per nonzero); with the split's own size only, dx takes one float
- * atomic per nonzero. */
+ * for matrices of 400,000 nonzeros or more holds the products of dx, sorted by
+ * target range (6 bytes per nonzero), unless targets or rows are too many for
+ * them.  The products are formed in units of 4096 items whatever s asks for;
+ * with the split's own size only (which follows s), dx takes one float atomic
+ * per nonzero. */
 LB_API lb_status_t lb_spmv_backward(const lb_csr_t *A, const void *x, lb_dtype_t x_dtype,
                                     const float *dy, float *dx, float *dvalues,
                                     const lb_schedule_t *s, void *workspace,

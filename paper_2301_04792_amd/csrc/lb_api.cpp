@@ -369,9 +369,10 @@ size_t ws_bytes_for(const lb_csr_t *A, const lb_schedule_t &s, int32_t k) {
 }
 
 // Workspace of the scatter by bins for A's dx (0 where it does not pay).  A
-// call with less workspace scatters with float atomics.
-size_t scatter_ws_bytes(const lb_csr_t *A) {
-    return lbk::bins_pay(A->cols, A->nnz) ? lbk::bins_ws_bytes(A->rows, A->cols, A->nnz) : 0;
+// call with less workspace scatters with float atomics.  csc: A is a CSC's view
+// by columns.
+size_t scatter_ws_bytes(const lb_csr_t *A, bool csc) {
+    return lbk::bins_pay(A->rows, A->cols, A->nnz, csc) ? lbk::bins_ws_bytes(A->rows, A->cols, A->nnz) : 0;
 }
 
 // ------------------------------------------------------------------ COO and CSC
@@ -869,7 +870,7 @@ LB_API lb_status_t lb_workspace_size(const lb_csr_t *A, const lb_schedule_t *s, 
         }
     }
     *bytes = ws_bytes_for(A, r, k);
-    if (k == 0) *bytes = std::max(*bytes, scatter_ws_bytes(A));
+    if (k == 0) *bytes = std::max(*bytes, scatter_ws_bytes(A, false));
     return LB_OK;
 }
 
@@ -1314,7 +1315,7 @@ LB_API lb_status_t lb_csc_workspace_size(const lb_csc_t *A, const lb_schedule_t 
     lb_schedule_t r;
     st = csc_schedule(s, &r);
     if (st != LB_OK) return st;
-    *bytes = std::max(ws_bytes_for(&c, r, 0), scatter_ws_bytes(&c));
+    *bytes = std::max(ws_bytes_for(&c, r, 0), scatter_ws_bytes(&c, true));
     return LB_OK;
 }
 
@@ -1333,7 +1334,7 @@ LB_API lb_status_t lb_spmv_csc(const lb_csc_t *A, const void *x, lb_dtype_t x_dt
     if (workspace_bytes < need || !workspace) return LB_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     if (A->rows == 0) return LB_OK;
-    const size_t bins = scatter_ws_bytes(&c);
+    const size_t bins = scatter_ws_bytes(&c, true);
     if (bins > 0 && workspace_bytes >= bins)
         return hip_status(lbk::binned_backward(to_dev(&c), nullptr, static_cast<const float *>(x), y, nullptr,
                                                workspace, hs));
@@ -1419,7 +1420,7 @@ LB_API lb_status_t lb_spmv_backward(const lb_csr_t *A, const void *x, lb_dtype_t
     const size_t need = ws_bytes_for(A, r, 0);
     if (workspace_bytes < need || !workspace) return LB_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    const size_t bins = dx ? scatter_ws_bytes(A) : 0;
+    const size_t bins = dx ? scatter_ws_bytes(A, false) : 0;
     if (bins > 0 && workspace_bytes >= bins)
         return hip_status(lbk::binned_backward(to_dev(A), x, dy, dx, dvalues, workspace, hs));
     if (dx) {

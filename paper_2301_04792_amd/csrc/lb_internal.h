@@ -241,17 +241,30 @@ hipError_t merge_backward(const csr_dev &A, const void *x, const float *dy, floa
                           float *prod = nullptr);
 
 // ---- the backward's scatter by bins (k_bins.hip) ----------------------------------------
-// Whether dx (A.cols targets, written whole) is summed by bins.  us, by bins and
-// by float atomics (backward with dvalues): 0.23M power-law nonzeros 24.4 / 20.8,
-// 0.48M uniform 22.3 / 39.3, 6.6M power-law 99 / 275, 32M uniform 348 / 1552, 32M
-// over 1000 columns 181 / 7934; a stencil of 5.2M 61.2 / 59.2.  CSC product:
-// 0.45M stencil 17.1 / 23.3, 30.8M power-law 214 / 959.  At most 512 bins (4.2M
-// targets): runs of a unit's bin are short past that (20M nonzeros over 4M
-// columns 543 / 988).
+// Whether dx (n targets, written whole) is summed by bins.  Atomics cost 22 ns more
+// per 1000 nonzeros (twice that on the few lines of 4 bins of targets or fewer), the
+// bins 6 us, 9 ns per 1000 targets (zeroed and added), 2 per 1000 rows (in units
+// twice as long) and 30 per 1000 words of run starts ((bins + 1) per unit, written
+// and read).  The weights are fitted to 65 random matrices, backward with dvalues,
+// and rounded toward atomics.  us, by bins and by atomics:
+//   bins taken: 0.4M nonzeros over 300,000 columns 27.5 / 30.5, 1M over 1M 56.7 /
+//   64.2, 4M over 4.19M 185 / 218, 4M in 32M rows over 10,000 148 / 329, 5M over 1M
+//   102 / 257, 32M over 1000 181 / 7934; stencils of 0.45M 13.6 / 14.7, 5.2M 42.3 /
+//   59.4, 21M 198 / 209 (222 / 214 with cold caches);
+//   atomics taken: 0.4M over 400,000 33.2 / 31.3, 0.64M over 1M 48.3 / 46.6, 2M over
+//   4.19M 133 / 118, 0.4M over 4.19M 66.0 / 38.3, 0.5M in 50M rows over 10,000 157 /
+//   89, over 4M 405 / 99, 4M in 50M rows over 4M 543 / 251.
+// by_rows: the CSC product (rows: A's columns), whose atomics come after a hash of
+// the unit's targets in LDS.  That is full in units of few rows: 0.4M nonzeros over
+// 4.19M targets in 50,000 rows 61 / 139, in 100,000 60 / 55, 0.4M over 1M in 50,000
+// 31 / 122.
+// At most 512 bins (4.2M targets): runs of a unit's bin are short past that (20M
+// nonzeros over 4M columns 543 / 988).  Fewer than 400,000 nonzeros: 0.23M power-law
+// 24.4 / 20.8.
 constexpr int64_t kBinMinNnz = 400000;
-bool bins_pay(int64_t n, int64_t nnz);
+bool bins_pay(int64_t rows, int64_t n, int64_t nnz, bool by_rows);
 size_t bins_ws_bytes(int64_t rows, int64_t n, int64_t nnz);
-// As merge_backward with dx; dx need not be cleared.  Needs bins_pay.
+// As merge_backward with dx; dx need not be cleared.  At most 512 bins of targets.
 hipError_t binned_backward(const csr_dev &A, const void *x, const float *dy, float *dx, float *dvalues, void *ws,
                            hipStream_t s);
 
