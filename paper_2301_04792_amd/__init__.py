@@ -266,6 +266,17 @@ def transpose_pattern(P: Pattern, rebuild: bool = False):
     return P._transposed
 
 
+def _split_bytes(c: _abi.CSR, s: _abi.Schedule) -> int:
+    """Bytes of the merge-path split alone: the backward's workspace where no
+    products of dx are kept in it."""
+    if s.kind == _abi.AUTO:
+        s = make_schedule("merge_path")
+    units, n = _abi.Schedule(), ctypes.c_size_t(0)
+    _abi.check(_lib.lb_resolve_schedule(ctypes.byref(c), 0, ctypes.byref(s), ctypes.byref(units)), "lb_resolve_schedule")
+    _abi.check(_lib.lb_workspace_size(ctypes.byref(c), ctypes.byref(units), 1, ctypes.byref(n)), "lb_workspace_size")
+    return int(n.value)
+
+
 def spmv_backward(A: CSR, x: torch.Tensor, dy: torch.Tensor, need_dx: bool = True, need_dvalues: bool = True,
                   schedule="merge_path", transposed=None, **params):
     """(dx, dvalues) of y = A x: dx = A^T dy, dvalues[j] = dy[row(j)] x[col(j)] (float32).
@@ -281,6 +292,9 @@ def spmv_backward(A: CSR, x: torch.Tensor, dy: torch.Tensor, need_dx: bool = Tru
         n = ctypes.c_size_t(0)
         _abi.check(_lib.lb_backward_transposed_workspace_size(ctypes.byref(c), ctypes.byref(s), ctypes.byref(n)),
                    "lb_backward_transposed_workspace_size")
+        if not (need_dx and need_dvalues):
+            at = _abi.CSR(c.cols, c.rows, c.nnz, c.row_offsets, c.col_idx, c.values, c.value_dtype)  # A^T's sizes
+            n.value = max(_split_bytes(c, s), _split_bytes(at, s))
         dx = torch.empty(A.shape[1], dtype=torch.float32, device=A.device) if need_dx else None
         dv = torch.empty(A.nnz, dtype=torch.float32, device=A.device) if need_dvalues else None
         ws = _workspace(max(n.value, 1), A.device)
@@ -291,6 +305,8 @@ def spmv_backward(A: CSR, x: torch.Tensor, dy: torch.Tensor, need_dx: bool = Tru
         return dx, dv
     n = ctypes.c_size_t(0)
     _abi.check(_lib.lb_workspace_size(ctypes.byref(c), ctypes.byref(s), 0, ctypes.byref(n)), "lb_workspace_size")
+    if not need_dx:
+        n.value = _split_bytes(c, s)
     dx = torch.empty(A.shape[1], dtype=torch.float32, device=A.device) if need_dx else None
     dv = torch.empty(A.nnz, dtype=torch.float32, device=A.device) if need_dvalues else None
     ws = _workspace(max(n.value, 1), A.device)
