@@ -108,10 +108,13 @@ typedef struct lb_csr_t {
  *                    band), a matrix with rows + nnz <= 256 * 2048 gets the
  *                    shortest unit of 128 x 4, 256 x 4 and 256 x 8 items
  *                    that gives at most 256 units, which lb_spmv runs as
- *                    one launch; lb_resolve_schedule reports the choice.  SpMM
- *                    and batched passes take up to 8 columns of X at a
- *                    time, fewer for large block_size * items_per_thread;
- *                    group-mapped derived from group_size (ignored).
+ *                    one launch; lb_resolve_schedule reports the choice.
+ *                    With k > 1, lb_spmm runs a unit of 256 x 8 items (the
+ *                    default, or named) as its two halves, and
+ *                    lb_batched_spmm's default is 512 x 8 where the batch
+ *                    fills 1024 such units, else 256 x 4; all k columns go
+ *                    in one pass over the matrix.  Group-mapped: derived
+ *                    from group_size (ignored).
  *  grid_size         blocks; 0 = one block per chunk of work.
  *  x_bands           LB_MERGE_PATH in lb_spmv: 1 or 2 (default 1).  With 2,
  *                    every merge-path unit is consumed by two blocks placed on
@@ -360,7 +363,9 @@ LB_API lb_status_t lb_spmv_noalloc(const lb_csr_t *A, const void *x, lb_dtype_t 
  * B(nz, col) as B(col_idx[nz], col)).  X row-major cols x k with leading
  * dimension ldx >= k; Y row-major rows x k float32 with ldy >= k,
  * overwritten.  1 <= k <= 64.  Same numerics and workspace rules as lb_spmv
- * (workspace from lb_workspace_size(A, s, k)). */
+ * (workspace from lb_workspace_size(A, s, k)).  A smaller workspace that holds
+ * the carries of 8 columns (4 or 2 where k is below 8 or 4) runs the product in
+ * passes of as many. */
 LB_API lb_status_t lb_spmm(const lb_csr_t *A, const void *X, lb_dtype_t x_dtype, int32_t k,
                            int64_t ldx, float *Y, int64_t ldy, const lb_schedule_t *s,
                            void *workspace, size_t workspace_bytes, void *stream);
@@ -420,8 +425,9 @@ LB_API lb_status_t lb_batched_workspace_size(const lb_batch_t *B, const lb_sched
  * total_rows x k float32, overwritten.  One launch splits the single merge
  * path of sum(m_b + nnz_b) items into units, one persistent launch (Sec. 5.1
  * persistent ranges) consumes every unit of every matrix, and one launch
- * adds the carries (per pass of up to 8 columns).  s->kind must be
- * LB_MERGE_PATH or LB_AUTO.  1 <= k <= 64. */
+ * adds the carries; a workspace smaller than lb_batched_workspace_size takes
+ * passes of 8 columns where it fits those.  s->kind must be LB_MERGE_PATH or
+ * LB_AUTO.  1 <= k <= 64. */
 LB_API lb_status_t lb_batched_spmm(const lb_batch_t *B, const void *X, lb_dtype_t x_dtype,
                                    int32_t k, float *Y, const lb_schedule_t *s, void *workspace,
                                    size_t workspace_bytes, void *stream);
@@ -445,8 +451,9 @@ LB_API lb_status_t lb_group_tile_owner(const lb_csr_t *A, int32_t tiles_per_grou
                                        void *stream);
 
 /* Time candidate schedules for A with k right-hand sides on `stream`
- * (synchronizing) using the caller's x/X, y/Y and workspace (at least
- * lb_autotune_workspace_size bytes), store the fastest in a process-wide
+ * (synchronizing) using the caller's x/X, y/Y and workspace (from
+ * lb_autotune_workspace_size; with less, down to the carries of lb_spmm's passes,
+ * the pick is the fastest with that workspace), store the fastest in a process-wide
  * cache and return it in *best.  A cache entry is keyed by the shape, k,
  * the value dtype and a fingerprint of the sparsity pattern (Sec. 6.2
  * picks a schedule per matrix), and belongs to the device it was timed on

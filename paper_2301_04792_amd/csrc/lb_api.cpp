@@ -300,10 +300,7 @@ lb_schedule_t heuristic(const lb_csr_t *A) {
     return s;
 }
 
-// *default_units: a merge-path schedule whose units the caller (or its tuned
-// pick) left open.
-lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_schedule_t *out,
-                    bool *default_units = nullptr) {
+lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_schedule_t *out) {
     if (!in || !out) return LB_ERR_INVALID_ARG;
     lb_schedule_t s = *in;
     if (s.kind == LB_AUTO) {
@@ -317,7 +314,6 @@ lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_sc
     }
     const lb_status_t st = fill_defaults(&s, out);
     if (st != LB_OK) return st;
-    if (default_units) *default_units = out->kind == LB_MERGE_PATH && s.block_size == 0 && s.items_per_thread == 0;
     // column bands and vector loads: lb_spmv only
     if ((out->x_bands != 1 || out->vector_width != 1) && k != 1) return LB_ERR_UNSUPPORTED;
     if (out->kind == LB_MERGE_PATH && k == 1 && s.block_size == 0 && s.items_per_thread == 0 && out->x_bands == 1 &&
@@ -337,15 +333,16 @@ lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_sc
     return LB_OK;
 }
 
-// Units of a product with k > 1 columns whose units were left open: half the
-// default.  A group of lanes walks its items one after the other (64 items in
-// each of 8 groups of a wavefront at k = 32 and 256 x 8), so shorter units end
-// sooner and small matrices fill more CUs.  256 x 4 against 256 x 8, us a call:
-// 5000 power-law rows, k = 64 20.9 / 30.8; 20,000 uniform rows, k = 13
-// 14.0 / 16.7; 490,000-row stencil, k = 8 28.4 / 34.3; 500,003 power-law rows,
-// k = 32 240.0 / 240.9.
-void spmm_units(int32_t k, bool default_units, lb_schedule_t *r) {
-    if (k > 1 && default_units) r->items_per_thread = kDefaultItems / 2;
+// Units of a product with k > 1 columns: one of 256 x 8 items, whether resolved
+// from open fields or named, is run as its two halves.  A group of lanes walks its
+// items one after the other (64 items in each of 8 groups of a wavefront at k = 32
+// and 256 x 8), so shorter units end sooner and small matrices fill more CUs.
+// 256 x 4 against 256 x 8, us a call: 5000 power-law rows, k = 64 20.9 / 30.8;
+// 20,000 uniform rows, k = 13 14.0 / 16.7; 490,000-row stencil, k = 8 28.4 / 34.3;
+// 500,003 power-law rows, k = 32 240.0 / 240.9.
+void spmm_halves(int32_t k, lb_schedule_t *r) {
+    if (k > 1 && r->kind == LB_MERGE_PATH && r->block_size == kDefaultBlock && r->items_per_thread == kDefaultItems)
+        r->items_per_thread = kDefaultItems / 2;
 }
 
 // Entry points other than lb_spmv take the plain merge-path consume only
@@ -858,10 +855,9 @@ LB_API lb_status_t lb_workspace_size(const lb_csr_t *A, const lb_schedule_t *s, 
     lb_status_t st = check_csr(A);
     if (st != LB_OK) return st;
     lb_schedule_t r;
-    bool default_units = false;
-    st = resolve(A, k, s, &r, &default_units);
+    st = resolve(A, k, s, &r);
     if (st != LB_OK) return st;
-    spmm_units(k, default_units, &r);
+    spmm_halves(k, &r);
     if (k == 0) {  // backward always runs on the merge-path split
         if (r.kind != LB_MERGE_PATH) {
             lb_schedule_t m{};
@@ -1378,15 +1374,18 @@ LB_API lb_status_t lb_spmm(const lb_csr_t *A, const void *X, lb_dtype_t x_dtype,
     if (x_dtype != A->value_dtype) return LB_ERR_UNSUPPORTED;
     if (A->cols * ldx > (int64_t(1) << 40) || A->rows * ldy > (int64_t(1) << 40)) return LB_ERR_OVERFLOW;
     lb_schedule_t r;
-    bool default_units = false;
-    st = resolve(A, k, s, &r, &default_units);
+    st = resolve(A, k, s, &r);
     if (st != LB_OK) return st;
-    spmm_units(k, default_units, &r);
     if (r.kind == LB_GROUP_MAPPED || r.kind == LB_WORK_QUEUE || one_band(r) != LB_OK) return LB_ERR_UNSUPPORTED;
-    // a smaller workspace runs the product in passes, then in longer units
+    // a smaller workspace runs the product in whole units, then in passes of fewer columns
+    const lb_schedule_t whole = r;
+    spmm_halves(k, &r);
     int32_t kc = k;
-    if (workspace_bytes < ws_bytes_for(A, r, kc)) kc = spmm_narrow_cols(k);
-    if (k > 1 && default_units && workspace_bytes < ws_bytes_for(A, r, kc)) r.items_per_thread = kDefaultItems;
+    const auto fits = [&](const lb_schedule_t &u) { return workspace_bytes >= ws_bytes_for(A, u, kc); };
+    if (!fits(r)) {
+        if (!fits(whole)) kc = spmm_narrow_cols(k);
+        if (!fits(r)) r = whole;
+    }
     const size_t need = ws_bytes_for(A, r, kc);
     if (need > 0 && (workspace_bytes < need || !workspace)) return LB_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t hs = static_cast<hipStream_t>(stream);

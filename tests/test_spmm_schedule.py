@@ -1,0 +1,57 @@
+"""lb_resolve_schedule tells what lb_spmm runs: the schedule that it reports, passed
+back, takes the same workspace and (on the GPU) gives the same bits."""
+import ctypes
+
+import pytest
+
+torch = pytest.importorskip("torch")
+lb = pytest.importorskip("paper_2301_04792_amd", reason="liblb.so not built")
+import synthetic as S  # noqa: E402
+from paper_2301_04792_amd import _abi  # noqa: E402
+from tests.gpu_util import assert_rows_close, oracle_spmm  # noqa: E402
+
+FAKE = 0x10000  # never dereferenced
+
+
+def _resolved(A, s, k):
+    out = _abi.Schedule()
+    assert _abi.load().lb_resolve_schedule(ctypes.byref(A), k, ctypes.byref(s), ctypes.byref(out)) == _abi.OK
+    return out
+
+
+@pytest.mark.parametrize("k", [1, 2, 8, 32, 64])
+@pytest.mark.parametrize("kind", ["merge_path", "auto"])
+@pytest.mark.parametrize("rows,nnz", [(4096, 64_248), (500_003, 11_700_000)])
+def test_resolved_schedule_takes_the_same_workspace(rows, nnz, kind, k):
+    A = _abi.CSR(rows, rows, nnz, FAKE, FAKE, FAKE, _abi.F32)
+    sizes = []
+    for s in (lb.make_schedule(kind), _resolved(A, lb.make_schedule(kind), k)):
+        n = ctypes.c_size_t(0)
+        assert _abi.load().lb_workspace_size(ctypes.byref(A), ctypes.byref(s), k, ctypes.byref(n)) == _abi.OK
+        sizes.append(n.value)
+    assert sizes[0] == sizes[1]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("k", [2, 24])
+def test_resolved_schedule_gives_the_same_bits(k):
+    A, _ = S.powerlaw_csr(7, 30_000, 20_000, 1.7, 9000, 0.1)
+    X = S.random_vector(3, A.n * k).reshape(A.n, k)
+    Ad, Xd = lb.CSR.from_host(A, "cuda:0"), torch.from_numpy(X).to("cuda:0")
+    c = Ad.c_struct()
+    Y = lb.spmm(Ad, Xd)
+    assert_rows_close(Y.cpu().numpy(), *oracle_spmm(A, X), what=f"k={k}")
+    back = _resolved(c, lb.make_schedule("merge_path"), k)
+    assert torch.equal(Y, lb.spmm(Ad, Xd, back))
+    # units of 256 x 8 items (as many as of 128 x 16) where the workspace is for those
+    # only: for all columns, then for eight of them
+    for cols in sorted({k, min(k, 8)}, reverse=True):
+        n = lb.workspace_size(Ad, "merge_path", k=cols, block_size=128, items_per_thread=16)
+        assert n < lb.workspace_size(Ad, "merge_path", k=cols)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        for s in (lb.make_schedule("merge_path"), back):
+            Z = torch.full_like(Y, 7.0)
+            st = lb._lib.lb_spmm(ctypes.byref(c), lb._ptr(Xd), 0, k, k, lb._ptr(Z), k, ctypes.byref(s), lb._ptr(ws), n,
+                                 lb._stream(Ad.device))
+            assert st == 0
+            assert_rows_close(Z.cpu().numpy(), *oracle_spmm(A, X), what=f"k={k}, workspace of {cols} columns")
