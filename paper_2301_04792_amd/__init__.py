@@ -129,6 +129,20 @@ def _workspace(nbytes: int, device, workspace=None):
     return torch.empty(int(nbytes), dtype=torch.uint8, device=device)
 
 
+def _sized_workspace(nbytes: int, device, workspace=None):
+    """A workspace and its bytes, for calls that also run with less than nbytes
+    (the caller's is passed on as it is)."""
+    if workspace is None or nbytes == 0:
+        return _workspace(nbytes, device), nbytes
+    return workspace, workspace.numel() * workspace.element_size()
+
+
+def _check_sized(status: int, what: str, nbytes: int, workspace):
+    if status == _abi.ERR_WORKSPACE_TOO_SMALL and workspace is not None:
+        raise ValueError(f"workspace too small: {what} takes {nbytes} bytes")
+    _abi.check(status, what)
+
+
 def resolve_schedule(A: CSR, schedule="merge_path", k: int = 1, **params) -> dict:
     s = make_schedule(schedule, **params)
     out = _abi.Schedule()
@@ -239,9 +253,9 @@ def spmm(A: CSR, X: torch.Tensor, schedule="merge_path", Y: torch.Tensor | None 
     _abi.check(_lib.lb_workspace_size(ctypes.byref(c), ctypes.byref(s), k, ctypes.byref(n)), "lb_workspace_size")
     if Y is None:
         Y = torch.empty((A.shape[0], k), dtype=torch.float32, device=A.device)
-    ws = _workspace(n.value, A.device, workspace)
-    _abi.check(_lib.lb_spmm(ctypes.byref(c), _ptr(X), _dtype_code(X), k, X.stride(0), _ptr(Y), Y.stride(0),
-                            ctypes.byref(s), _ptr(ws), n.value, _stream(A.device)), "lb_spmm")
+    ws, nbytes = _sized_workspace(n.value, A.device, workspace)
+    _check_sized(_lib.lb_spmm(ctypes.byref(c), _ptr(X), _dtype_code(X), k, X.stride(0), _ptr(Y), Y.stride(0),
+                              ctypes.byref(s), _ptr(ws), nbytes, _stream(A.device)), "lb_spmm", n.value, workspace)
     return Y
 
 
@@ -406,9 +420,9 @@ def batched_spmm(batch: Batch, X: torch.Tensor, schedule="auto", Y=None, workspa
                "lb_batched_workspace_size")
     if Y is None:
         Y = torch.empty((batch.total_rows, k), dtype=torch.float32, device=batch.device)
-    ws = _workspace(n.value, batch.device, workspace)
-    _abi.check(_lib.lb_batched_spmm(ctypes.byref(c), _ptr(X2), _dtype_code(X2), k, _ptr(Y), ctypes.byref(s),
-                                    _ptr(ws), n.value, _stream(batch.device)), "lb_batched_spmm")
+    ws, nbytes = _sized_workspace(n.value, batch.device, workspace)
+    _check_sized(_lib.lb_batched_spmm(ctypes.byref(c), _ptr(X2), _dtype_code(X2), k, _ptr(Y), ctypes.byref(s),
+                                      _ptr(ws), nbytes, _stream(batch.device)), "lb_batched_spmm", n.value, workspace)
     return Y.reshape(-1) if vec else Y
 
 
@@ -687,11 +701,11 @@ def _format_spmv(fn_size, fn, what, A, x, schedule, y, workspace, params):
     n = ctypes.c_size_t(0)
     a = A.c_struct()
     _abi.check(fn_size(ctypes.byref(a), ctypes.byref(s), ctypes.byref(n)), what + " workspace size")
-    ws = _workspace(n.value, A.device, workspace)
+    ws, nbytes = _sized_workspace(n.value, A.device, workspace)
     if y is None:
         y = torch.empty(A.shape[0], dtype=torch.float32, device=A.device)
-    _abi.check(fn(ctypes.byref(a), _ptr(x), _dtype_code(x), _ptr(y), ctypes.byref(s), _ptr(ws),
-                  0 if ws is None else ws.numel(), _stream(A.device)), what)
+    _check_sized(fn(ctypes.byref(a), _ptr(x), _dtype_code(x), _ptr(y), ctypes.byref(s), _ptr(ws), nbytes,
+                    _stream(A.device)), what, n.value, workspace)
     return y
 
 
