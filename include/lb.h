@@ -571,8 +571,9 @@ LB_API lb_status_t lb_spgemm_compute(const lb_csr_t *A, const lb_csr_t *B, const
  * an indexed tile set) and relaxes every out-edge of its vertices under the
  * schedule s; the vertices that improve form the next frontier, each listed
  * once.  The host launches again while the frontier holds vertices (Sec. 5.3; a
- * merge-path launch may take several small frontiers), reading the frontier size from the device once per batch of iterations, so these
- * calls synchronize `stream`.
+ * merge-path launch may take several small frontiers), reading the frontier size
+ * from the device once per batch of iterations, so these calls synchronize
+ * `stream`.
  * Schedules: LB_THREAD_MAPPED (a thread per frontier vertex, block_size as
  * for SpMV), LB_WORK_QUEUE (group_size in [8, 1024]: frontier chunks handed
  * out by a device work queue), LB_GROUP_MAPPED with group_size a power of two in [8, 1024]
@@ -580,20 +581,20 @@ LB_API lb_status_t lb_spgemm_compute(const lb_csr_t *A, const lb_csr_t *B, const
  * and get_tile over the group's vertices), LB_AUTO = the rule of Sec. 6.2
  * as for SpMV (merge-path unless (rows < 500 or cols < 500) and
  * nnz < 10000; then thread-mapped, or group-mapped with at least 8 lanes).
- * LB_MERGE_PATH (256 threads x 8
- * merge items per unit; other block_size / items_per_thread values return
- * LB_ERR_UNSUPPORTED): per iteration the frontier's out-degrees are
- * prefix-summed on the device, the merge of those offsets with the
- * frontier's edges is split into equal units (Sec. 5.2.1) and a persistent
- * launch walks them.  grid_size 0 = the resident grid (CUs x occupancy).
+ * LB_MERGE_PATH (no parameters: block_size / items_per_thread other than 0 or
+ * 256 / 8 return LB_ERR_UNSUPPORTED): the frontier's edges, numbered through
+ * the out-degrees that it carries, are cut into units of 2048, which the blocks
+ * of a persistent launch take in equal ranges (Sec. 5.2.1 with vertices without
+ * edges left out); a frontier of one unit or less is one block's, which goes on
+ * with the next.  grid_size 0 = the resident grid (CUs x occupancy).
  * max_iterations 0 = rows + 1 (enough for any graph with weights >= 0); a
  * frontier still non-empty after max_iterations returns
  * LB_ERR_NOT_CONVERGED (the outputs then hold upper bounds).
  * *iterations (host, may be NULL) receives the number of non-empty
  * frontiers processed.  source in [0, rows). */
 
-/* Workspace bytes for lb_sssp / lb_bfs on G (about 4 * rows int32, plus the
- * merge-path split over at most rows + nnz items).  Host-only. */
+/* Workspace bytes for lb_sssp / lb_bfs on G (about 4 * rows int32, plus 8 bytes
+ * per 2048 of rows + nnz, kept as they were and not used).  Host-only. */
 LB_API lb_status_t lb_traversal_workspace_size(const lb_csr_t *G, size_t *bytes);
 
 /* Single-source shortest paths: dist (rows float32, overwritten) receives

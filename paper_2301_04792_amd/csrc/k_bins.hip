@@ -19,7 +19,10 @@
 //                    adds those to out (one coalesced
 //                    float atomic per target and range of units).
 // The sums are float64 so that a target with thousands of terms (a capped row
-// of a power-law matrix in the CSC product) loses nothing to their order.
+// of a power-law matrix in the CSC product) loses little to their order: terms
+// that lanes of a wavefront share are added in float32 first (at most six
+// additions deep, 6 * 2^-24 of their absolute sum), and so are the results of
+// the blocks that hold parts of a target.
 // Bytes a nonzero: 8 read, 6 written and 6 read, all streams, in place of one
 // scattered atomic.  (With the bins whole in memory, each unit's run of a bin
 // placed after the last unit's, a counting pass over the columns came first:
@@ -268,7 +271,9 @@ __global__ __launch_bounds__(kBinBlock) void bin_products(
 
 // Adds v to the bin's sum k, for the lanes with `in`.  A target that many lanes
 // share (a capped row in the CSC product) is summed over them first: 84 us
-// against 115 for 30.8M entries of which half fall on a few targets.
+// against 115 for 30.8M entries of which half fall on a few targets.  In float32:
+// in float64, two lane moves a step, the CSC product of a 1M-row power-law matrix
+// took 233 us against 225, its error 7.8e-8 against 8.2e-8.
 __device__ __forceinline__ void bin_sum_add(double *sum, float v, uint16_t k, bool in) {
     const int32_t k0 = __builtin_amdgcn_readfirstlane(k);
     const bool same = in && k == k0;

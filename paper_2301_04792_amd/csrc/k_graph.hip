@@ -270,8 +270,9 @@ struct edge_args {
 
 // A frontier of one unit of edges or less is the work of one block, which goes on
 // with the next one itself, up to this many iterations a launch: it knows the next
-// frontier's size, and a launch, its gap and its start cost more than the unit
-// (MEASURED4).
+// frontier's size, and a launch, its gap and its start cost more than the unit: a
+// grid of 200 x 200, 399 iterations, BFS 3.76 ms launched one by one (9.4 us an
+// iteration), 1.87 so (4.7); SSSP 4.11 and 2.22.
 constexpr int32_t kSmallIters = 256;
 
 // Inclusive prefix sum over the block of a 64-bit value; s_wave holds BLOCK/64.

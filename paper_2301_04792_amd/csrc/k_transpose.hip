@@ -488,11 +488,14 @@ hipError_t backward_transposed(const csr_dev &A, const int32_t *at_ro, const int
                                const void *x, const float *dy, float *dx, float *dvalues, int block, int items,
                                void *ws, bool products, hipStream_t s) {
     // The pass over A that dvalues needs also leaves the products, so that the
-    // SpMV on A^T gathers one word a nonzero instead of two (values and dy): 1M
-    // power-law rows, 31.6M nonzeros, both gradients 497 -> 383 us; a stencil of
-    // 5.2M 49.1 / 50.8.  Without dvalues the pass would come on top (the stencil's
-    // dx alone 29.2 / 45.0, 1.6M power-law 27.2 / 33.8, 31.6M 342 / 229), so dx
-    // alone gathers both.
+    // SpMV on A^T gathers one word a nonzero instead of two (values and dy).  Both
+    // gradients, us with products / with values: 1M power-law rows, 31.6M nonzeros
+    // 383 / 497; 5M uniform over 1M columns 130 / 178, 1M 38.3 / 49.5.  Where the
+    // gathers are local they cost about as much as the products' own bytes: stencils
+    // of 5.2M 47.2 / 46.8 (56.6 / 57.1 with cold caches), 21M 133 / 126 (153 / 160);
+    // sizes do not tell the two apart.  dx alone would pay for the whole pass (with
+    // values / with products: the 5.2M stencil 29.2 / 45.0, 1.6M power-law 27.2 / 33.8,
+    // 31.6M 342 / 229), so it gathers both.
     float *prod = nullptr;
     if (products && dx && dvalues)
         prod = reinterpret_cast<float *>(static_cast<char *>(ws) +

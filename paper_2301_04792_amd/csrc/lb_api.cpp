@@ -471,7 +471,7 @@ lb_status_t traversal_cfg(const lb_csr_t *G, const lb_schedule_t *in, lbk::trav_
             if (c.tiles_per_group != 1 && c.tiles_per_group != c.group) return LB_ERR_UNSUPPORTED;
             if (s.kind == LB_WORK_QUEUE && c.tiles_per_group != c.group) return LB_ERR_UNSUPPORTED;
             break;
-        case LB_MERGE_PATH:  // one configuration: 256 threads x 8 merge items per unit
+        case LB_MERGE_PATH:  // one configuration, named 256 x 8
             if ((s.block_size && s.block_size != 256) || (s.items_per_thread && s.items_per_thread != 8))
                 return LB_ERR_UNSUPPORTED;
             break;
