@@ -208,9 +208,15 @@ __global__ __launch_bounds__(BLOCK) void merge_spmm_consume(
 // L1 has 256 lines, each held until its request is back, which bounds requests
 // in flight (139 G nonzeros/s with X in L2, 106 with 200,000-row members).
 // kAhead 2, 4 and 16: 3.86, 3.89 and 4.00 ms; k = 32: 253, 254 and 242 us.
+// ONE: a lane holds the whole row (k = 2 and 4) and owns ITEMS merge items, four to
+// eight, of which eight rows ahead would load most twice: four are in flight.
+// 500,000 rows of 9, k = 2 42.8 us, 55.9 with eight (units of 256 x 4 there); BF16,
+// k = 4 42.6 and 56.8.  BF16, k = 8: two lanes of four columns 62.2 us, one of eight
+// 76.8.
 constexpr int kAhead = 8;
+constexpr int kAheadOne = 4;
 
-template <int BLOCK, int ITEMS, int V, bool BATCHED, typename VT>
+template <int BLOCK, int ITEMS, int V, bool ONE, bool BATCHED, typename VT>
 __global__ __launch_bounds__(BLOCK) void merge_spmm_rows(
     int32_t rows, int32_t nnz, int32_t T, int32_t kc, int lg, const int32_t *__restrict__ ro,
     const int32_t *__restrict__ ci, const VT *__restrict__ val, const VT *__restrict__ X, int64_t ldx,
@@ -219,6 +225,7 @@ __global__ __launch_bounds__(BLOCK) void merge_spmm_rows(
     const int64_t *__restrict__ nnz_base, const int64_t *__restrict__ col_base) {
     constexpr int W = BLOCK * ITEMS;
     constexpr int NW = BLOCK / kWave;
+    constexpr int AHEAD = ONE ? kAheadOne : kAhead;
     __shared__ int32_t s_buf[W];  // row ends [0, nrows), then X rows of the nonzeros [nrows, nrows + nnzs)
     __shared__ float s_val[W];
     __shared__ float s_wv[NW * kMaxCols];
@@ -342,17 +349,17 @@ __global__ __launch_bounds__(BLOCK) void merge_spmm_rows(
         };
         int32_t end = it < it1 ? s_re[it] : INT32_MAX;  // the nonzero before which row it closes
         const VT *xc = X + c0;
-        for (int32_t j = d - lo; j < jt1; j += kAhead) {
-            float g[kAhead][V], v[kAhead];
+        for (int32_t j = d - lo; j < jt1; j += AHEAD) {
+            float g[AHEAD][V], v[AHEAD];
 #pragma unroll
-            for (int a = 0; a < kAhead; ++a) {
+            for (int a = 0; a < AHEAD; ++a) {
                 const int32_t ja = j + a < jt1 ? j + a : jt1 - 1;
                 v[a] = s_val[ja];
                 load_cols<V>(xc + static_cast<int64_t>(s_xr[ja]) * ldx, g[a]);
             }
 #pragma unroll
-            for (int a = 0; a < kAhead; ++a) {
-                if (a == kAhead / 2) {
+            for (int a = 0; a < AHEAD; ++a) {
+                if (a == AHEAD / 2) {
 #pragma unroll
                     for (int c = 0; c < V; ++c) {
                         half[c] = part[c];
@@ -456,9 +463,12 @@ static uint32_t spmm_grid(K kern, int block, int64_t T) {
 template <int BLOCK, int ITEMS, int V, bool BATCHED, typename VT>
 static hipError_t spmm_rows_launch(const spmm_problem &P, const merge_ws &w, const int32_t *part_mat, int64_t T,
                                    const VT *X, int32_t kc, int64_t ldx, float *Y, int64_t ldy, hipStream_t s) {
-    auto kern = merge_spmm_rows<BLOCK, ITEMS, V, BATCHED, VT>;
     int lg = 0;
     while ((V << lg) < kc) ++lg;
+    auto kern = merge_spmm_rows<BLOCK, ITEMS, V, false, BATCHED, VT>;
+    if constexpr (V <= 4) {
+        if (lg == 0) kern = merge_spmm_rows<BLOCK, ITEMS, V, true, BATCHED, VT>;
+    }
     prof_scope p(s, BATCHED ? "batched_consume" : "merge_consume");
     hipLaunchKernelGGL(kern, dim3(spmm_grid<BATCHED>(kern, BLOCK, T)), dim3(BLOCK), 0, s, P.rows, P.nnz,
                        static_cast<int32_t>(T), kc, lg, P.ro, P.ci, static_cast<const VT *>(P.val), X, ldx, Y, ldy,
@@ -478,13 +488,14 @@ static hipError_t spmm_pass(const spmm_problem &P, const merge_ws &w, const int3
                            static_cast<int32_t>(T), P.ro, P.ci, static_cast<const VT *>(P.val), X, ldx, Y, ldy,
                            w.part_i, w.part_j, w.carry_row, w.carry_val, part_mat, P.nnz_base, P.col_base);
         e = hipGetLastError();
-    } else if (kc < 4) {
-        e = spmm_rows_launch<BLOCK, ITEMS, 2, BATCHED, VT>(P, w, part_mat, T, X, kc, ldx, Y, ldy, s);
-    } else if (sizeof(VT) == 4 || kc < 8) {
-        e = spmm_rows_launch<BLOCK, ITEMS, 4, BATCHED, VT>(P, w, part_mat, T, X, kc, ldx, Y, ldy, s);
     } else {
-        e = spmm_rows_launch<BLOCK, ITEMS, (sizeof(VT) == 2 ? 8 : 4), BATCHED, VT>(P, w, part_mat, T, X, kc, ldx, Y,
-                                                                                  ldy, s);
+        switch (spmm_lane_cols(kc, sizeof(VT) == 2)) {
+            case 2: e = spmm_rows_launch<BLOCK, ITEMS, 2, BATCHED, VT>(P, w, part_mat, T, X, kc, ldx, Y, ldy, s); break;
+            case 4: e = spmm_rows_launch<BLOCK, ITEMS, 4, BATCHED, VT>(P, w, part_mat, T, X, kc, ldx, Y, ldy, s); break;
+            default:
+                e = spmm_rows_launch<BLOCK, ITEMS, (sizeof(VT) == 2 ? 8 : 4), BATCHED, VT>(P, w, part_mat, T, X, kc, ldx,
+                                                                                          Y, ldy, s);
+        }
     }
     if (e != hipSuccess) return e;
     return launch_fixup(T, P.rows, kc, w.carry_row, w.carry_val, Y, ldy, s, BATCHED ? "batched_fixup" : "merge_fixup");

@@ -333,16 +333,25 @@ lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_sc
     return LB_OK;
 }
 
+constexpr int64_t kFewUnits = 512;
+bool few_units(int64_t rows, int64_t nnz) {
+    return lbk::merge_units(rows, nnz, kDefaultBlock * kDefaultItems) <= kFewUnits;
+}
+
 // Units of a product with k > 1 columns: one of 256 x 8 items, whether resolved
 // from open fields or named, is run as its two halves.  A group of lanes walks its
 // items one after the other (64 items in each of 8 groups of a wavefront at k = 32
 // and 256 x 8), so shorter units end sooner and small matrices fill more CUs.
 // 256 x 4 against 256 x 8, us a call: 5000 power-law rows, k = 64 20.9 / 30.8;
 // 20,000 uniform rows, k = 13 14.0 / 16.7; 490,000-row stencil, k = 8 28.4 / 34.3;
-// 500,003 power-law rows, k = 32 240.0 / 240.9.
-void spmm_halves(int32_t k, lb_schedule_t *r) {
-    if (k > 1 && r->kind == LB_MERGE_PATH && r->block_size == kDefaultBlock && r->items_per_thread == kDefaultItems)
-        r->items_per_thread = kDefaultItems / 2;
+// 500,003 power-law rows, k = 32 240.0 / 240.9.  Where one lane holds a row it has
+// ITEMS of them only, and the halves' second split, carries and fix-up cost more
+// than they spread, unless there are few units: k = 2, 3M rows of 2 (4.4k units)
+// 47.3 / 41.7, 300,000 of 7 (1.2k) 19.8 / 17.5, 20,000 power-law (0.2k) 12.5 / 13.7.
+void spmm_halves(const lb_csr_t *A, int32_t k, lb_schedule_t *r) {
+    if (k < 2 || r->kind != LB_MERGE_PATH || r->block_size != kDefaultBlock || r->items_per_thread != kDefaultItems) return;
+    if (lbk::spmm_one_lane(k, A->value_dtype == LB_BF16) && !few_units(A->rows, A->nnz)) return;
+    r->items_per_thread = kDefaultItems / 2;
 }
 
 // Entry points other than lb_spmv take the plain merge-path consume only
@@ -857,7 +866,7 @@ LB_API lb_status_t lb_workspace_size(const lb_csr_t *A, const lb_schedule_t *s, 
     lb_schedule_t r;
     st = resolve(A, k, s, &r);
     if (st != LB_OK) return st;
-    spmm_halves(k, &r);
+    spmm_halves(A, k, &r);
     if (k == 0) {  // backward always runs on the merge-path split
         if (r.kind != LB_MERGE_PATH) {
             lb_schedule_t m{};
@@ -1379,7 +1388,7 @@ LB_API lb_status_t lb_spmm(const lb_csr_t *A, const void *X, lb_dtype_t x_dtype,
     if (r.kind == LB_GROUP_MAPPED || r.kind == LB_WORK_QUEUE || one_band(r) != LB_OK) return LB_ERR_UNSUPPORTED;
     // a smaller workspace runs the product in whole units, then in passes of fewer columns
     const lb_schedule_t whole = r;
-    spmm_halves(k, &r);
+    spmm_halves(A, k, &r);
     int32_t kc = k;
     const auto fits = [&](const lb_schedule_t &u) { return workspace_bytes >= ws_bytes_for(A, u, kc); };
     if (!fits(r)) {
@@ -1484,11 +1493,15 @@ static lb_status_t resolve_batched(const lb_batch_t *B, int32_t k, const lb_sche
         // on half as many places of the batch, and the X rows of those stay in
         // L2 (159M misses against 246M).  512 matrices, 436M nonzeros, k = 8:
         // 3.37 ms, 256 x 8 4.36; 207M nonzeros, k = 11 1.95 / 2.55, k = 2
-        // 0.92 / 1.06.  Fewer than four such units a CU leave it idle: 32
-        // matrices, 0.55M nonzeros, 17.4 us against 14.9 with 256 x 4.
-        const bool large = lbk::merge_units(B->total_rows, B->total_nnz, 512 * 8) >= 1024;
+        // 0.92 / 1.06.  Fewer than eight such units a CU leave it idle: 32
+        // matrices, 0.55M nonzeros, 17.4 us against 14.9 with 256 x 4; one of 5M
+        // (1.3k units), BF16, k = 8 77.9 and 70.8.  Where a lane holds a whole row,
+        // 256 x 4 only for few units: 64 of 3000 rows, k = 4 28.8 us, 256 x 8 29.5,
+        // BF16 27.5 and 24.3.
+        const bool one = lbk::spmm_one_lane(k, B->value_dtype == LB_BF16);
+        const bool large = lbk::merge_units(B->total_rows, B->total_nnz, 512 * 8) >= 2048;
         out->block_size = large ? 512 : 256;
-        out->items_per_thread = large ? 8 : 4;
+        out->items_per_thread = large || (one && !few_units(B->total_rows, B->total_nnz)) ? 8 : 4;
     }
     return one_band(*out);
 }
@@ -1522,11 +1535,20 @@ LB_API lb_status_t lb_batched_spmm(const lb_batch_t *B, const void *X, lb_dtype_
     if (st != LB_OK) return st;
     const lbk::batch_dev d = to_dev(B);
     int32_t kc = std::max(k, kBatchedNarrow);
-    if (workspace_bytes < lbk::batched_ws_bytes(d, r.block_size, r.items_per_thread, kc)) kc = kBatchedNarrow;
-    // (units chosen by the caller or its tuned pick fit their own size)
-    if (k > 1 && default_units && workspace_bytes < lbk::batched_ws_bytes(d, r.block_size, r.items_per_thread, kc)) {
-        r.block_size = kDefaultBlock;
-        r.items_per_thread = kDefaultItems;
+    const auto fits = [&](int32_t block, int32_t items, int32_t cols) {
+        return workspace_bytes >= lbk::batched_ws_bytes(d, block, items, cols);
+    };
+    // A smaller workspace: longer units (for batches whose default they once were),
+    // then passes.  (Units chosen by the caller or its tuned pick fit their own size.)
+    const bool open = k > 1 && default_units;
+    if (!fits(r.block_size, r.items_per_thread, kc)) {
+        if (open && lbk::merge_units(B->total_rows, B->total_nnz, 512 * 8) >= 1024 && fits(512, 8, kc)) {
+            r.block_size = 512, r.items_per_thread = 8;
+        } else {
+            kc = kBatchedNarrow;
+            if (open && !fits(r.block_size, r.items_per_thread, kc))
+                r.block_size = kDefaultBlock, r.items_per_thread = kDefaultItems;
+        }
     }
     const size_t need = lbk::batched_ws_bytes(d, r.block_size, r.items_per_thread, kc);
     if (need > 0 && (workspace_bytes < need || !workspace)) return LB_ERR_WORKSPACE_TOO_SMALL;

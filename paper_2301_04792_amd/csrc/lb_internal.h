@@ -229,6 +229,10 @@ hipError_t merge_spmv_planned_consume(const csr_dev &A, const plan_dev &pl, cons
 // y = A x with a built plan; ws holds plan_ws_bytes(...).
 hipError_t planned_spmv(const csr_dev &A, const plan_dev &pl, const void *x, float *y, void *ws, hipStream_t s);
 
+// Columns of X that a lane holds in a product of kc > 1 columns (16 bytes where
+// there are enough), and whether that is the whole row.
+inline int spmm_lane_cols(int32_t kc, bool bf16) { return kc < 4 ? 2 : (bf16 && kc > 8 ? 8 : 4); }
+inline bool spmm_one_lane(int32_t kc, bool bf16) { return kc > 1 && kc <= spmm_lane_cols(kc, bf16); }
 // The workspace is merge_ws_bytes(T, kc_max): passes of at most kc_max columns.
 hipError_t merge_spmm(const csr_dev &A, const void *X, int32_t k, int64_t ldx, float *Y, int64_t ldy,
                       int block, int items, void *ws, int32_t kc_max, hipStream_t s);

@@ -51,3 +51,21 @@ def test_csc():
     assert_rows_close(lb.spmv_csc(T, xd, workspace=split).cpu().numpy(), *oracle_spmv(A, x), what="csc")
     with pytest.raises(ValueError):
         lb.spmv_csc(T, xd, workspace=split[:256])
+
+
+@pytest.mark.parametrize("k", [2, 8, 24])
+def test_batched_of_larger_units(k):
+    """Batches of 1024 to 2047 units of 512 x 8 items: their workspace still serves."""
+    import oracle
+    B = S.batched_powerlaw(8, 8, 20_000, 50_000)
+    Bd = lb.Batch.from_host(B, DEV)
+    units = (Bd.total_rows + Bd.total_nnz + 4095) // 4096
+    assert 1024 <= units < 2048, units
+    X = S.random_vector(9, B.total_cols * k).reshape(-1, k)
+    Xd = torch.from_numpy(X).to(DEV)
+    words = lambda n: -(-4 * n // 256) * 256  # noqa: E731
+    n = 2 * words(units + 1) + words(units) + words(max(k, 8) * units) + words(units + 1)
+    ref, scale = oracle.batched_spmm(B, X), oracle.batched_spmm(B, X, abs_terms=True)
+    Y = lb.batched_spmm(Bd, Xd, workspace=torch.empty(n, dtype=torch.uint8, device=DEV))
+    assert_rows_close(Y.cpu().numpy(), ref, scale, what=f"batched k={k}")
+    assert_rows_close(lb.batched_spmm(Bd, Xd).cpu().numpy(), ref, scale, what=f"batched k={k}, its own workspace")

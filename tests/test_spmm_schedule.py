@@ -2,6 +2,7 @@
 back, takes the same workspace and (on the GPU) gives the same bits."""
 import ctypes
 
+import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -30,6 +31,50 @@ def test_resolved_schedule_takes_the_same_workspace(rows, nnz, kind, k):
         assert _abi.load().lb_workspace_size(ctypes.byref(A), ctypes.byref(s), k, ctypes.byref(n)) == _abi.OK
         sizes.append(n.value)
     assert sizes[0] == sizes[1]
+
+
+def _bytes(rows, nnz, k, dtype=_abi.F32, **units):
+    n = ctypes.c_size_t(0)
+    A = _abi.CSR(rows, rows, nnz, FAKE, FAKE, FAKE, dtype)
+    assert _abi.load().lb_workspace_size(ctypes.byref(A), ctypes.byref(lb.make_schedule("merge_path", **units)), k,
+                                         ctypes.byref(n)) == _abi.OK
+    return n.value
+
+
+@pytest.mark.parametrize("dtype", [_abi.F32, _abi.BF16])
+@pytest.mark.parametrize("k,one_lane", [(2, True), (3, False), (4, True), (5, False), (8, False), (32, False)])
+def test_whole_units_where_a_lane_holds_a_row(k, one_lane, dtype):
+    """Halves of 256 x 8 cost more than they spread where a lane holds a whole row of
+    X, past 512 units (128 x 16 and 128 x 8 items have as many units)."""
+    whole, halves = {"block_size": 128, "items_per_thread": 16}, {"block_size": 128, "items_per_thread": 8}
+    few, many = 512 * 2048, 512 * 2048 + 1  # merge items
+    assert _bytes(100_000, few - 100_000, k, dtype) == _bytes(100_000, few - 100_000, k, dtype, **halves)
+    assert _bytes(100_000, many - 100_000, k, dtype) == _bytes(100_000, many - 100_000, k, dtype, **(whole if one_lane else halves))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("k", [2, 3, 4, 8])
+@pytest.mark.parametrize("items", [512 * 2048, 512 * 2048 + 1])
+def test_sizes_around_the_rule(items, k, dtype):
+    rng = np.random.default_rng(k)
+    lengths = rng.integers(0, 9, 150_000)
+    lengths[7] = 40_000  # longer than units
+    lengths[-1] += items - 150_000 - lengths.sum()
+    A, _ = S.csr._from_lengths(5, lengths, 600_000)
+    assert A.m + A.nnz == items
+    X = S.random_vector(3, A.n * k).reshape(A.n, k)
+    if dtype == "bf16":
+        A, X = A.with_values(S.to_bf16_bits(A.values)), S.to_bf16_bits(X)
+        Xd = torch.from_numpy(X.view("int16")).view(torch.bfloat16).to("cuda:0")
+    else:
+        Xd = torch.from_numpy(X).to("cuda:0")
+    Ad = lb.CSR.from_host(A, "cuda:0")
+    want = oracle_spmm(A, X)
+    assert_rows_close(lb.spmm(Ad, Xd).cpu().numpy(), *want, what=f"k={k} {dtype}")
+    base = lambda n: torch.tensor([0, n], dtype=torch.int64, device="cuda:0")  # noqa: E731
+    B = lb.Batch(Ad.row_offsets, Ad.col_idx, Ad.values, base(A.m), base(A.nnz), base(A.n))
+    assert_rows_close(lb.batched_spmm(B, Xd).cpu().numpy(), *want, what=f"batched k={k} {dtype}")
 
 
 @pytest.mark.gpu
