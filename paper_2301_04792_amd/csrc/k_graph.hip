@@ -608,15 +608,17 @@ hipError_t run_traversal(const csr_dev &G, int32_t source, float *dist, int32_t 
     }
     trav_args t{G.ro, G.ci, static_cast<const float *>(G.val), dist, depth, w.stamp,
                 nullptr, nullptr, nullptr, nullptr, nullptr, w.counters + 3, nullptr, nullptr, 0};
-    // Batches of 4 iterations up to 16, then doubling to 32: a power-law graph ends
-    // within 16, and what is launched past the end is wasted (batches of 4, 8 and 16
-    // launched 28 iterations for 13); a long chain or grid pays for each wait.
+    // The size is read after 4, 8, 12, 16, 28, 32, 60, 92, ... launches: a power-law
+    // graph ends within 16, and what is launched past the end is wasted (28 for 13);
+    // a long chain or grid pays for each wait.  Read at 32 after 16, a graph of 20
+    // iterations paid for more launches than at 28 (work queue, 100,000 vertices of
+    // three edges, BFS 1.03 ms against 0.93).
     int32_t launched = 0;
     if (c.kind == LB_MERGE_PATH && c.grid <= 0) c.grid = resident_blocks(advance_merge_kernel<BFS>, kEdgeBlock);
     int32_t host[kTravDone + 3] = {}, rounds = 0;
     *converged = false;
     for (;;) {
-        const int32_t batch = launched < 16 ? 4 : (launched < 32 ? launched : 32);
+        const int32_t batch = launched < 16 ? 4 : (launched < 28 ? 12 : (launched < 32 ? 4 : (launched < 60 ? 28 : 32)));
         for (int k = 0; k < batch && launched < max_iter; ++k, ++launched) {
             t.iter = launched;
             t.q_in = w.queue[launched & 1];
