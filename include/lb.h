@@ -109,13 +109,14 @@ typedef struct lb_csr_t {
  *                    shortest unit of 128 x 4, 256 x 4 and 256 x 8 items
  *                    that gives at most 256 units, which lb_spmv runs as
  *                    one launch; lb_resolve_schedule reports the choice.
- *                    With k > 1, lb_spmm runs a unit of 256 x 8 items (the
- *                    default, or named) as its two halves (k = 2 and 4: up to
- *                    512 units), and lb_batched_spmm's default is 512 x 8
- *                    where the batch fills 2048 such units, else 256 x 4
- *                    (k = 2 and 4: 256 x 8 past 512 units); all k columns
- *                    go in one pass over the matrix.  Group-mapped: derived
- *                    from group_size (ignored).
+ *                    With k > 1, lb_spmm runs units of 256 x 8 items, the
+ *                    default or named, as their two halves where the matrix
+ *                    has up to 512 of them; its default past that is 256 x 4
+ *                    (256 x 8 for k = 2 and 4).  lb_batched_spmm's default
+ *                    is 512 x 8 where the batch fills 2048 such units, else
+ *                    256 x 4 (k = 2 and 4: 256 x 8 past 512 units).  All k
+ *                    columns go in one pass over the matrix.  Group-mapped:
+ *                    derived from group_size (ignored).
  *  grid_size         blocks; 0 = one block per chunk of work.
  *  x_bands           LB_MERGE_PATH in lb_spmv: 1 or 2 (default 1).  With 2,
  *                    every merge-path unit is consumed by two blocks placed on

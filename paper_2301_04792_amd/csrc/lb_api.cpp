@@ -300,7 +300,13 @@ lb_schedule_t heuristic(const lb_csr_t *A) {
     return s;
 }
 
-lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_schedule_t *out) {
+constexpr int64_t kFewUnits = 512;
+bool few_units(int64_t rows, int64_t nnz) {
+    return lbk::merge_units(rows, nnz, kDefaultBlock * kDefaultItems) <= kFewUnits;
+}
+
+// *open: a merge-path schedule whose units the caller (or its tuned pick) left open.
+lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_schedule_t *out, bool *open = nullptr) {
     if (!in || !out) return LB_ERR_INVALID_ARG;
     lb_schedule_t s = *in;
     if (s.kind == LB_AUTO) {
@@ -314,10 +320,11 @@ lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_sc
     }
     const lb_status_t st = fill_defaults(&s, out);
     if (st != LB_OK) return st;
+    const bool units_open = out->kind == LB_MERGE_PATH && s.block_size == 0 && s.items_per_thread == 0;
+    if (open) *open = units_open;
     // column bands and vector loads: lb_spmv only
     if ((out->x_bands != 1 || out->vector_width != 1) && k != 1) return LB_ERR_UNSUPPORTED;
-    if (out->kind == LB_MERGE_PATH && k == 1 && s.block_size == 0 && s.items_per_thread == 0 && out->x_bands == 1 &&
-        out->vector_width == 1) {
+    if (units_open && k == 1 && out->x_bands == 1 && out->vector_width == 1) {
         // Default units on a small matrix: the shortest unit (128 x 4, 256 x 4
         // or 256 x 8 items) that keeps the one-launch form (at most
         // kSelfSplitUnits units) spreads the matrix over the most CUs, each
@@ -330,28 +337,26 @@ lb_status_t resolve(const lb_csr_t *A, int32_t k, const lb_schedule_t *in, lb_sc
             }
         }
     }
+    // More columns, and more units than spmm_halves takes: 256 x 4 too (490,000-row
+    // stencil, k = 8 29.8 us, 256 x 8 35.9; 500,003 power-law rows, k = 32 240.0 and
+    // 240.9; 3M rows of 2, k = 32 146 and 131), unless one lane holds a row: it has
+    // ITEMS of them only, and more units mean more splits, carries and fix-up (k = 2,
+    // 3M rows of 2 47.3 and 41.7, 300,000 of 7 19.8 and 17.5).
+    if (units_open && k > 1 && !lbk::spmm_one_lane(k, A->value_dtype == LB_BF16) && !few_units(A->rows, A->nnz))
+        out->items_per_thread = kDefaultItems / 2;
     return LB_OK;
 }
 
-constexpr int64_t kFewUnits = 512;
-bool few_units(int64_t rows, int64_t nnz) {
-    return lbk::merge_units(rows, nnz, kDefaultBlock * kDefaultItems) <= kFewUnits;
-}
-
-// Units of a product with k > 1 columns: one of 256 x 8 items, whether resolved
-// from open fields or named, is run as its two halves.  A group of lanes walks its
-// items one after the other (64 items in each of 8 groups of a wavefront at k = 32
-// and 256 x 8), so shorter units end sooner and small matrices fill more CUs.
-// 256 x 4 against 256 x 8, us a call: 5000 power-law rows, k = 64 20.9 / 30.8;
-// 20,000 uniform rows, k = 13 14.0 / 16.7; 490,000-row stencil, k = 8 28.4 / 34.3;
-// 500,003 power-law rows, k = 32 240.0 / 240.9.  Where one lane holds a row it has
-// ITEMS of them only, and the halves' second split, carries and fix-up cost more
-// than they spread, unless there are few units: k = 2, 3M rows of 2 (4.4k units)
-// 47.3 / 41.7, 300,000 of 7 (1.2k) 19.8 / 17.5, 20,000 power-law (0.2k) 12.5 / 13.7.
+// Up to kFewUnits units of 256 x 8 items, a product with k > 1 columns runs each as
+// its two halves, whether resolved from open fields or named: a group of lanes walks
+// its items one after the other (64 items in each of 8 groups of a wavefront at k =
+// 32), so shorter units end sooner and fill more CUs.  256 x 4 against 256 x 8, us a
+// call: 5000 power-law rows, k = 64 20.9 / 30.8; 20,000 uniform rows, k = 13 14.0 /
+// 16.7; 30,000 rows of 20, k = 16 17.0 / 18.9.
 void spmm_halves(const lb_csr_t *A, int32_t k, lb_schedule_t *r) {
-    if (k < 2 || r->kind != LB_MERGE_PATH || r->block_size != kDefaultBlock || r->items_per_thread != kDefaultItems) return;
-    if (lbk::spmm_one_lane(k, A->value_dtype == LB_BF16) && !few_units(A->rows, A->nnz)) return;
-    r->items_per_thread = kDefaultItems / 2;
+    if (k > 1 && r->kind == LB_MERGE_PATH && r->block_size == kDefaultBlock && r->items_per_thread == kDefaultItems &&
+        few_units(A->rows, A->nnz))
+        r->items_per_thread = kDefaultItems / 2;
 }
 
 // Entry points other than lb_spmv take the plain merge-path consume only
@@ -1383,11 +1388,13 @@ LB_API lb_status_t lb_spmm(const lb_csr_t *A, const void *X, lb_dtype_t x_dtype,
     if (x_dtype != A->value_dtype) return LB_ERR_UNSUPPORTED;
     if (A->cols * ldx > (int64_t(1) << 40) || A->rows * ldy > (int64_t(1) << 40)) return LB_ERR_OVERFLOW;
     lb_schedule_t r;
-    st = resolve(A, k, s, &r);
+    bool open = false;
+    st = resolve(A, k, s, &r, &open);
     if (st != LB_OK) return st;
     if (r.kind == LB_GROUP_MAPPED || r.kind == LB_WORK_QUEUE || one_band(r) != LB_OK) return LB_ERR_UNSUPPORTED;
     // a smaller workspace runs the product in whole units, then in passes of fewer columns
-    const lb_schedule_t whole = r;
+    lb_schedule_t whole = r;
+    if (open && k > 1) whole.items_per_thread = kDefaultItems;
     spmm_halves(A, k, &r);
     int32_t kc = k;
     const auto fits = [&](const lb_schedule_t &u) { return workspace_bytes >= ws_bytes_for(A, u, kc); };
@@ -1634,7 +1641,12 @@ LB_API lb_status_t lb_autotune(const lb_csr_t *A, const void *X, lb_dtype_t x_dt
     // replaces it only if it is more than 2 % faster, so timing noise does
     // not flip the choice between equivalent configurations.
     lb_schedule_t best_s = heuristic(A);
-    fill_defaults(&best_s, &best_s);
+    if (k > 1) {
+        const lb_schedule_t rule = best_s;
+        (void)resolve(A, k, &rule, &best_s);
+    } else {
+        fill_defaults(&best_s, &best_s);
+    }
     float best_ms = 1e30f;
     {
         auto run0 = [&]() -> lb_status_t {

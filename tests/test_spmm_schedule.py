@@ -45,11 +45,15 @@ def _bytes(rows, nnz, k, dtype=_abi.F32, **units):
 @pytest.mark.parametrize("k,one_lane", [(2, True), (3, False), (4, True), (5, False), (8, False), (32, False)])
 def test_whole_units_where_a_lane_holds_a_row(k, one_lane, dtype):
     """Halves of 256 x 8 cost more than they spread where a lane holds a whole row of
-    X, past 512 units (128 x 16 and 128 x 8 items have as many units)."""
+    X, past 512 units (128 x 16 and 128 x 8 items have as many units); past those, a
+    named 256 x 8 is what it says."""
     whole, halves = {"block_size": 128, "items_per_thread": 16}, {"block_size": 128, "items_per_thread": 8}
     few, many = 512 * 2048, 512 * 2048 + 1  # merge items
     assert _bytes(100_000, few - 100_000, k, dtype) == _bytes(100_000, few - 100_000, k, dtype, **halves)
     assert _bytes(100_000, many - 100_000, k, dtype) == _bytes(100_000, many - 100_000, k, dtype, **(whole if one_lane else halves))
+    named = {"block_size": 256, "items_per_thread": 8}
+    assert _bytes(100_000, few - 100_000, k, dtype, **named) == _bytes(100_000, few - 100_000, k, dtype, **halves)
+    assert _bytes(100_000, many - 100_000, k, dtype, **named) == _bytes(100_000, many - 100_000, k, dtype, **whole)
 
 
 @pytest.mark.gpu
@@ -72,6 +76,10 @@ def test_sizes_around_the_rule(items, k, dtype):
     Ad = lb.CSR.from_host(A, "cuda:0")
     want = oracle_spmm(A, X)
     assert_rows_close(lb.spmm(Ad, Xd).cpu().numpy(), *want, what=f"k={k} {dtype}")
+    # the workspace of whole units and of the columns of one pass, 8, 4 or 2, as before the one-pass form
+    narrow = lb.workspace_size(Ad, "merge_path", k={2: 2, 3: 2, 4: 4, 8: 8}[k], block_size=128, items_per_thread=16)
+    ws = torch.empty(narrow, dtype=torch.uint8, device="cuda:0")
+    assert_rows_close(lb.spmm(Ad, Xd, workspace=ws).cpu().numpy(), *want, what=f"k={k} {dtype}, workspace of one pass")
     base = lambda n: torch.tensor([0, n], dtype=torch.int64, device="cuda:0")  # noqa: E731
     B = lb.Batch(Ad.row_offsets, Ad.col_idx, Ad.values, base(A.m), base(A.nnz), base(A.n))
     assert_rows_close(lb.batched_spmm(B, Xd).cpu().numpy(), *want, what=f"batched k={k} {dtype}")
