@@ -359,7 +359,8 @@ __global__ __launch_bounds__(kSumBlock) void bin_sum(int32_t nb, int32_t n, int3
 bool bins_pay(int64_t rows, int64_t n, int64_t nnz, bool by_rows) {
     if (n > static_cast<int64_t>(kBinMax) * kBinCols || nnz < kBinMinNnz) return false;
     if (by_rows) {
-        if (n <= 8 && (n == 1 ? 3 : n) * nnz <= 8000000 && 4 * rows <= 3 * nnz) return false;
+        const bool dense = n <= 2 ? rows <= 4 * nnz : 4 * rows <= 3 * nnz;
+        if (n <= 8 && (n == 1 ? 3 : n) * nnz <= 8000000 && dense) return false;
         if (8 * rows <= nnz) return true;
     }
     const int64_t nb = (n + kBinCols - 1) >> kBinShift, starts = (nb + 1) * merge_units(rows, nnz, kBinW);

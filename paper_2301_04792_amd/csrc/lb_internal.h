@@ -264,7 +264,7 @@ hipError_t merge_backward(const csr_dev &A, const void *x, const float *dy, floa
 // 31 / 122.  A few targets never fill it, and their bins' sums meet in a few LDS
 // words: 0.5M nonzeros into 2 targets 59 / 20, 2M into 4 57 / 41, 4M into 2 75 / 53;
 // 8M into 2 84 / 91, 4M into 4 64 / 71, 0.5M into 16 34 / 41, into 4 from 2M columns
-// 28 / 44.
+// 28 / 44, into 1 from those 25 / 21.
 // At most 512 bins (4.2M targets): runs of a unit's bin are short past that (20M
 // nonzeros over 4M columns 543 / 988).  Fewer than 400,000 nonzeros: 0.23M power-law
 // 24.4 / 20.8.

@@ -55,6 +55,7 @@ def test_csc_of_few_columns(tiles, targets, nnz, bins):
 
 @pytest.mark.parametrize("tiles,targets,nnz,bins", [(20_000, 2, 500_000, False), (300_000, 4, 2_000_000, False), (20_000, 2, 4_000_000, False),
                                                     (20_000, 2, 4_000_001, True), (20_000, 8, 1_000_000, False), (20_000, 9, 500_000, True),
-                                                    (20_000, 1, 4_000_000, True), (2_000_000, 4, 500_000, True)])
+                                                    (20_000, 1, 4_000_000, True), (2_000_000, 4, 500_000, True),
+                                                    (2_000_000, 1, 500_000, False), (2_000_001, 1, 500_000, True)])
 def test_csc_of_few_rows(tiles, targets, nnz, bins):
     assert _csc_by_bins(targets, tiles, nnz) == bins
