@@ -306,7 +306,7 @@ def spmv_backward(A: CSR, x: torch.Tensor, dy: torch.Tensor, need_dx: bool = Tru
         n = ctypes.c_size_t(0)
         _abi.check(_lib.lb_backward_transposed_workspace_size(ctypes.byref(c), ctypes.byref(s), ctypes.byref(n)),
                    "lb_backward_transposed_workspace_size")
-        if not (need_dx and need_dvalues):
+        if not (need_dx and need_dvalues) and n.value >= 4 * c.nnz:  # with room for products
             at = _abi.CSR(c.cols, c.rows, c.nnz, c.row_offsets, c.col_idx, c.values, c.value_dtype)  # A^T's sizes
             n.value = max(_split_bytes(c, s), _split_bytes(at, s))
         dx = torch.empty(A.shape[1], dtype=torch.float32, device=A.device) if need_dx else None
@@ -319,7 +319,7 @@ def spmv_backward(A: CSR, x: torch.Tensor, dy: torch.Tensor, need_dx: bool = Tru
         return dx, dv
     n = ctypes.c_size_t(0)
     _abi.check(_lib.lb_workspace_size(ctypes.byref(c), ctypes.byref(s), 0, ctypes.byref(n)), "lb_workspace_size")
-    if not need_dx:
+    if not need_dx and n.value >= 6 * c.nnz:  # with room for dx's products
         n.value = _split_bytes(c, s)
     dx = torch.empty(A.shape[1], dtype=torch.float32, device=A.device) if need_dx else None
     dv = torch.empty(A.nnz, dtype=torch.float32, device=A.device) if need_dvalues else None
